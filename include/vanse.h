@@ -86,7 +86,7 @@ typedef struct {
 
 /* Bytes of device workspace the lattice described by *d needs (256-byte
  * aligned).  Layout: two population buffers, phi, optional phi(t+1),
- * solid-flag, force and drag planes, a density scratch plane and reduction
+ * solid-flag, force and drag planes, a velocity store and reduction
  * space.  VANSE_ERR_INVALID_ARG for a lattice whose population buffer (nine
  * planes of the storage type, rows padded to 64 nodes) would reach 4 GiB --
  * the step kernels address it with 32-bit offsets -- or with more than 65535
@@ -261,14 +261,13 @@ int vanse_observe(vanse_lattice *h, double *out, void *stream);
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * observables of vanse_observe, bitwise the same values, computed without
- * the lattice workspace's scratch -- the density of every node and of its
- * neighbours is formed again from the populations, and the FP64 block
- * partials and the reduction records live in a static device array of the
- * library (about 5.3 MB, held by every device the library runs on until the
- * process ends).  Allocates nothing.  Limit: ceil(nx/256) * ny <= 131072
- * (for example 4096 x 8192 or 8192 x 4096); larger lattices get
- * VANSE_ERR_INVALID_ARG before any device work.  Calls that overlap on one
- * device share the array and race: serialize them (one stream, or events).
+ * the lattice workspace's scratch -- the FP64 block partials and the
+ * reduction records live in a static device array of the library (about
+ * 5.3 MB, held by every device the library runs on until the process ends).
+ * Allocates nothing.  Limit: ceil(nx/256) * ny <= 131072 (for example 4096 x
+ * 8192 or 8192 x 4096); larger lattices get VANSE_ERR_INVALID_ARG before any
+ * device work.  Calls that overlap on one device share the array and race:
+ * serialize them (one stream, or events).
  * `out` is HOST memory (4 doubles); synchronizes the stream; returns
  * VANSE_ERR_DIVERGED (after filling out) when out[3] > 0. */
 int vanse_observe_noalloc(vanse_lattice *h, double *out, void *stream);

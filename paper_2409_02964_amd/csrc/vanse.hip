@@ -59,8 +59,25 @@ int compute_bytes(int precision) { return precision == VANSE_F64 ? 8 : 4; }
 
 int pitch_of(int nx) { return (nx + 63) / 64 * 64; }
 
+// Launch shape of the read-out: strips of READ_W columns, and rows per
+// workgroup so that about 2048 workgroups of four waves (eight per CU, every
+// wave slot of the chip) cover the lattice in one round; small lattices get
+// one row per workgroup.  A function of the sizes alone: it fixes the order
+// of the FP64 sums.
+struct ReadShape {
+  int strips, rows;
+  long long blocks;
+};
+ReadShape read_shape(int nx, int ny) {
+  ReadShape r;
+  r.strips = (nx + READ_W - 1) / READ_W;
+  r.rows = (int)(((long long)r.strips * ny + 2047) / 2048);
+  r.blocks = (long long)r.strips * ((ny + r.rows - 1) / r.rows);
+  return r;
+}
+
 struct Layout {
-  size_t pop[2], phi, phin, nbr, fx, fy, beta, drho, uprev, partials, partials2, result, badcount,
+  size_t pop[2], phi, phin, nbr, fx, fy, beta, uprev, partials, partials2, result, badcount,
       check, total;
   // a moving phi: phi(t+2) and the second step's force field and drag
   // coefficient of a two-step hand-over (vanse_set_void_fraction_next2)
@@ -115,9 +132,8 @@ int make_layout(const vanse_desc* d, Layout* L) {
   }
   L->beta = 0;
   if (d->has_drag) { L->beta = off; off = align256(off + plane * cb); }
-  L->drho = off; off = align256(off + plane * cb);
   L->uprev = off; off = align256(off + 2 * plane * cb);
-  L->max_partials = (long long)((d->nx + 255) / 256) * d->ny;
+  L->max_partials = read_shape(d->nx, d->ny).blocks;
   L->partials = off; off = align256(off + L->max_partials * NOBS * sizeof(double));
   L->partials2 = off; off = align256(off + 1024 * NOBS * sizeof(double));
   L->result = off; off = align256(off + NOBS * sizeof(double));
@@ -1020,14 +1036,13 @@ int vanse_set_check_interval(vanse_lattice* h, int64_t k) {
 }
 
 // Macroscopic read-out (rho, u, p; any may be null) and, with `part`, the
-// FP64 block partials of the observables into part.  plane: delta rho goes
-// through the workspace's scratch plane (two passes), else the second pass
-// forms every node's delta rho from its populations (no scratch plane).
+// FP64 partials of the observables into part (read_shape().blocks records).
 static int moments_into(vanse_lattice* h, double* rho, double* ux, double* uy, double* p,
-                        double* part, bool plane, hipStream_t st, bool keep_u) {
+                        double* part, hipStream_t st, bool keep_u) {
   if (int rc = check_ready(h)) return rc;
   if (!h->state_set) return fail(VANSE_ERR_STATE, "populations not initialised");
   const Geo G = make_geo(h);
+  const ReadShape R = read_shape(h->d.nx, h->d.ny);
   const int rc = by_precision(h, [&](auto* s_tag, auto* t_tag, auto shift) -> int {
     using S = std::remove_pointer_t<decltype(s_tag)>;
     using T = std::remove_pointer_t<decltype(t_tag)>;
@@ -1035,21 +1050,21 @@ static int moments_into(vanse_lattice* h, double* rho, double* ux, double* uy, d
     const StepPhys<T> ph = make_phys<T>(h);
     const S* buf = (const S*)(h->ws + h->L.pop[h->cur]);
     const T* phi = (const T*)(h->ws + h->L.phi);
-    T* drho = plane ? (T*)(h->ws + h->L.drho) : nullptr;
     const uint16_t* nbr = h->d.has_mask ? (const uint16_t*)(h->ws + h->L.nbr) : nullptr;
-    if (plane)
-      hipLaunchKernelGGL((moments_rho<S, T, SH>), field_grid(h), dim3(256), 0, st, G, buf, phi, ph, drho, nbr);
     const T* fx = h->d.has_force_field ? (const T*)(h->ws + h->L.fx) : nullptr;
     const T* fy = h->d.has_force_field ? (const T*)(h->ws + h->L.fy) : nullptr;
     const T* beta = h->d.has_drag ? (const T*)(h->ws + h->L.beta) : nullptr;
-    return by_variant(h, [&](auto walls, auto feat) -> int {
-      (void)walls;
-      T* up = keep_u ? (T*)(h->ws + h->L.uprev) : nullptr;
-      hipLaunchKernelGGL((moments_out<S, T, SH, decltype(feat)::value>), field_grid(h), dim3(256), 0, st, G,
-                         buf, phi, ph, drho, fx, fy, beta, rho, ux, uy, p, part, up,
-                         (int)(keep_u && h->uprev_valid), nbr);
-      return VANSE_OK;
-    });
+    T* up = keep_u ? (T*)(h->ws + h->L.uprev) : nullptr;
+    const int had = keep_u && h->uprev_valid;
+    const bool gen = h->d.has_mask || h->d.bc_x == VANSE_WALL || h->uw_lo != 0.0 || h->uw_hi != 0.0 ||
+                     h->nee_lo || h->nee_hi;
+    if (gen)
+      hipLaunchKernelGGL((read_out<S, T, SH, true>), dim3((unsigned)R.blocks), dim3(256), 0, st, G, buf, phi, ph,
+                         fx, fy, beta, rho, ux, uy, p, part, up, had, nbr, R.strips, R.rows);
+    else
+      hipLaunchKernelGGL((read_out<S, T, SH, false>), dim3((unsigned)R.blocks), dim3(256), 0, st, G, buf, phi, ph,
+                         fx, fy, beta, rho, ux, uy, p, part, up, had, nbr, R.strips, R.rows);
+    return VANSE_OK;
   });
   if (rc) return rc;
   HIP_TRY(hipGetLastError());
@@ -1059,7 +1074,7 @@ static int moments_into(vanse_lattice* h, double* rho, double* ux, double* uy, d
 static int moments(vanse_lattice* h, double* rho, double* ux, double* uy, double* p, bool partials,
                    void* stream, bool keep_u) {
   double* part = partials ? (double*)(h ? h->ws + h->L.partials : nullptr) : nullptr;
-  return moments_into(h, rho, ux, uy, p, part, true, static_cast<hipStream_t>(stream), keep_u);
+  return moments_into(h, rho, ux, uy, p, part, static_cast<hipStream_t>(stream), keep_u);
 }
 
 int vanse_read_moments(vanse_lattice* h, double* rho, double* ux, double* uy, double* p, void* stream) {
@@ -1091,7 +1106,13 @@ int vanse_read_populations(vanse_lattice* h, double* f, void* stream) {
 // Fixed-order reduction of n block partials (in) to one record (res), through
 // at most 1024 chunk records (mid); enqueued only.
 static int reduce_blocks(const double* in, long long n, double* mid, double* res, hipStream_t st) {
-  // level 1: at most 1024 chunks; level 2: one workgroup
+  // up to 4096 records (read_shape gives more only beyond a million columns):
+  // one workgroup; else at most 1024 chunks and then one workgroup
+  if (n <= 4096) {
+    hipLaunchKernelGGL(reduce_partials, dim3(1), dim3(256), 0, st, in, n, n, res);
+    HIP_TRY(hipGetLastError());
+    return VANSE_OK;
+  }
   const long long chunk = (n + 1023) / 1024;
   const long long nchunks = (n + chunk - 1) / chunk;
   hipLaunchKernelGGL(reduce_partials, dim3((unsigned)nchunks), dim3(256), 0, st, in, n, chunk, mid);
@@ -1103,7 +1124,7 @@ static int reduce_blocks(const double* in, long long n, double* mid, double* res
 // Reduce the block partials of the last moments pass to one record in the
 // workspace (enqueued only).
 static int reduce_on_device(vanse_lattice* h, hipStream_t st) {
-  const long long n = (long long)((h->d.nx + 255) / 256) * h->d.ny;
+  const long long n = read_shape(h->d.nx, h->d.ny).blocks;
   return reduce_blocks((const double*)(h->ws + h->L.partials), n, (double*)(h->ws + h->L.partials2),
                        (double*)(h->ws + h->L.result), st);
 }
@@ -1144,8 +1165,8 @@ int vanse_observe_noalloc(vanse_lattice* h, double* out, void* stream) {
   double* mid = sp + kScratchBlocks * NOBS;
   double* res = mid + 1024 * NOBS;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (int rc = moments_into(h, nullptr, nullptr, nullptr, nullptr, part, false, st, false)) return rc;
-  if (int rc = reduce_blocks(part, nblk, mid, res, st)) return rc;
+  if (int rc = moments_into(h, nullptr, nullptr, nullptr, nullptr, part, st, false)) return rc;
+  if (int rc = reduce_blocks(part, read_shape(h->d.nx, h->d.ny).blocks, mid, res, st)) return rc;
   double rec[NOBS];
   HIP_TRY(hipMemcpyAsync(rec, res, NOBS * sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -1676,7 +1697,7 @@ int vanse_batch_residual(vanse_batch* b, double* out, void* stream) {
     vanse_lattice* h = b->lats[k];
     had[k] = h->uprev_valid;
     if (int rc = moments(h, nullptr, nullptr, nullptr, nullptr, true, stream, true)) return rc;
-    const long long nblk = (long long)((h->d.nx + 255) / 256) * h->d.ny;
+    const long long nblk = read_shape(h->d.nx, h->d.ny).blocks;
     if (int rc = reduce_blocks((const double*)(h->ws + h->L.partials), nblk, (double*)(h->ws + h->L.partials2),
                                recs + k * NOBS, st))
       return rc;
