@@ -282,7 +282,11 @@ int vanse_residual(vanse_lattice *h, double *out, void *stream);
 
 /* Launch shape of the step kernel: threads per workgroup (64, 128, 256 or
  * 512; a workgroup owns threads-4 columns) and rows swept per workgroup
- * (>= 1).  threads = 0 or rows = 0 restores the size-based default. */
+ * (>= 1).  threads = 0 or rows = 0 restores the size-based default, which on
+ * lattices too small to fill the GPU replaces this row sweep by a kernel that
+ * advances up to four steps per launch, with bitwise the same results (the
+ * number of launches of a call stays nsteps modulo two).
+ * vanse_get_tiling reports the row sweep's shape either way. */
 int vanse_set_tiling(vanse_lattice *h, int threads, int rows);
 int vanse_get_tiling(const vanse_lattice *h, int *threads, int *rows,
                      int *workgroups);

@@ -1,9 +1,10 @@
 """Build libvanse.so for gfx950 with hipcc (in-tree).
 
-Five translation units compiled in parallel and linked into one shared
-library: ``csrc/vanse.hip`` (the C ABI, set-up and read-out kernels) and
+Six translation units compiled in parallel and linked into one shared
+library: ``csrc/vanse.hip`` (the C ABI, set-up and read-out kernels),
 ``csrc/step_{f64,f32,f32s,f16s}.hip`` (the step-kernel instances of each
-storage precision, from ``csrc/step_inst.hpp``).
+storage precision, from ``csrc/step_inst.hpp``) and ``csrc/tile.hip`` (the
+tile kernel of small lattices).
 """
 from __future__ import annotations
 
@@ -17,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libvanse.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = [os.path.join(HERE, "csrc", f) for f in
-           ("step_f32.hip", "step_f64.hip", "step_f32s.hip", "step_f16s.hip", "vanse.hip")]
+           ("step_f32.hip", "step_f64.hip", "step_f32s.hip", "step_f16s.hip", "tile.hip", "vanse.hip")]
 INCLUDE = [os.path.join(ROOT, "include"), os.path.join(HERE, "csrc")]
 
 HIPCC_FLAGS = [

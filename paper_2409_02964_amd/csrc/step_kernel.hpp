@@ -226,6 +226,266 @@ enum : int {
 // for velocity-like fields.
 __device__ __forceinline__ bool solid_bit(unsigned nb, int i) { return (nb >> i) & 1u; }
 
+// ---- the arithmetic of one node ---------------------------------------------
+// Shared by the row-sweep kernel below and the tile kernel, so that both round
+// alike: -ffp-contract=on fuses within one source expression only.
+
+// Deviations q of the nine pulled stored values f from the rest state
+template <typename S, typename T, bool SHIFT, typename V>
+__device__ __forceinline__ void deviations(const V (&f)[9], T phi, const StepPhys<T>& ph, T (&q)[9]) {
+  if (SHIFT) {  // only half storage carries a scale (2^-e)
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+      q[i] = sizeof(S) == 2 ? static_cast<T>(f[i]) * ph.inv_scale : static_cast<T>(f[i]);
+  } else {
+    q[0] = static_cast<T>(f[0]) - (phi * ph.rho0 - ph.rest0_k);
+#pragma unroll
+    for (int i = 1; i < 5; ++i) q[i] = static_cast<T>(f[i]) - ph.rest_axis;
+#pragma unroll
+    for (int i = 5; i < 9; ++i) q[i] = static_cast<T>(f[i]) - ph.rest_diag;
+  }
+}
+
+// Stored values of post-collision deviations o on a node whose next pull runs
+// at the void fraction phi (+ dphi when it moves: rest_0 changes by rho0
+// d_t phi, which shifted storage takes out here)
+template <typename S, typename T, bool SHIFT, int FEAT>
+__device__ __forceinline__ void stored(T (&o)[9], T phi, T dphi, const StepPhys<T>& ph, S (&v)[9]) {
+  if (SHIFT && (FEAT & FEAT_DYNPHI)) o[0] -= ph.rho0 * dphi;
+  if (SHIFT) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) v[i] = static_cast<S>(sizeof(S) == 2 ? o[i] * ph.scale : o[i]);
+  } else {
+    v[0] = static_cast<S>(o[0] + (phi * ph.rho0 - ph.rest0_k));
+#pragma unroll
+    for (int i = 1; i < 5; ++i) v[i] = static_cast<S>(o[i] + ph.rest_axis);
+#pragma unroll
+    for (int i = 5; i < 9; ++i) v[i] = static_cast<S>(o[i] + ph.rest_diag);
+  }
+}
+
+// Rows of M (Eq. A1) applied to the deviations
+template <typename T>
+__device__ __forceinline__ void moments_of(const T (&q)[9], RowState<T>& r) {
+  const T sa = (q[1] + q[2]) + (q[3] + q[4]);
+  const T sd = (q[5] + q[6]) + (q[7] + q[8]);
+  r.dm0 = q[0] + (sa + sd);
+  r.jx = (q[1] - q[3]) + ((q[5] - q[6]) + (q[8] - q[7]));
+  r.jy = (q[2] - q[4]) + ((q[5] + q[6]) - (q[7] + q[8]));
+  r.me = T(-4) * q[0] - sa + T(2) * sd;
+  r.mep = T(4) * q[0] - T(2) * sa + sd;
+  r.mqx = T(-2) * (q[1] - q[3]) + ((q[5] - q[6]) + (q[8] - q[7]));
+  r.mqy = T(-2) * (q[2] - q[4]) + ((q[5] + q[6]) - (q[7] + q[8]));
+  r.mpxx = (q[1] + q[3]) - (q[2] + q[4]);
+  r.mpxy = (q[5] + q[7]) - (q[6] + q[8]);
+}
+
+// delta-rho of the eight neighbours, by direction of Eq. (5)
+template <typename T>
+struct RhoAround {
+  T E, N, W, S, NE, NW, SW, SE;
+};
+
+// Stage B of a node: F (Eq. 13 and F^B), u (Eq. 7) and the products that the
+// penalty derivatives act on; solid neighbours take the centre's delta-rho
+template <int FEAT, typename T>
+__device__ __forceinline__ void velocity_of(RhoAround<T> n, const RowState<T>& r, T ffx, T ffy,
+                                            const StepPhys<T>& ph, U4<T>& a, U2<T>& b, T& Fx, T& Fy,
+                                            T& m0, T& rho) {
+  if constexpr ((FEAT & FEAT_MASK) != 0) {
+    const unsigned nb = r.nb;
+    const T rc = r.drho;
+    n.E = solid_bit(nb, 1) ? rc : n.E;
+    n.N = solid_bit(nb, 2) ? rc : n.N;
+    n.W = solid_bit(nb, 3) ? rc : n.W;
+    n.S = solid_bit(nb, 4) ? rc : n.S;
+    n.NE = solid_bit(nb, 5) ? rc : n.NE;
+    n.NW = solid_bit(nb, 6) ? rc : n.NW;
+    n.SW = solid_bit(nb, 7) ? rc : n.SW;
+    n.SE = solid_bit(nb, 8) ? rc : n.SE;
+  }
+  const T grx = stencil_dx(n.E, n.W, n.NE, n.SE, n.NW, n.SW);
+  const T gry = stencil_dy(n.N, n.S, n.NE, n.NW, n.SE, n.SW);
+  const T phi = r.phi;
+  const T kf = ((FEAT & FEAT_SCHEME) && ph.model_b) ? T(1) : phi;
+  const T kp = (ph.kappa - kf) * T(1.0 / 3.0);  // Eq. (13); kappa - 1 for model B
+  const T sg = ph.scale_by_phi ? phi : T(1);
+  Fx = kp * grx + sg * ph.gx;
+  Fy = kp * gry + sg * ph.gy;
+  if (FEAT & FEAT_FORCE) {
+    Fx += ffx;
+    Fy += ffy;
+  }
+  m0 = phi * ph.rho0 + r.dm0;
+  T ux, uy;
+  if (FEAT & FEAT_DRAG) {
+    // F = F' - phi beta (u - u_s) with u = (j + F/2)/m0: solved for u
+    const T d = phi * r.beta;
+    const T inv = recip(m0 + T(0.5) * d);
+    ux = (r.jx + T(0.5) * (Fx + d * ph.usx)) * inv;
+    uy = (r.jy + T(0.5) * (Fy + d * ph.usy)) * inv;
+    Fx -= d * (ux - ph.usx);
+    Fy -= d * (uy - ph.usy);
+  } else {
+    const T inv_m0 = recip(m0);
+    ux = (r.jx + T(0.5) * Fx) * inv_m0;
+    uy = (r.jy + T(0.5) * Fy) * inv_m0;
+  }
+  rho = ph.rho0 + r.drho;
+  a.ux = ux; a.uy = uy; a.mux = m0 * ux; a.rux = rho * ux;
+  b.muy = m0 * uy; b.ruy = rho * uy;
+}
+
+// Velocity data of a node and its neighbours
+template <typename T>
+struct VelAround {
+  U4<T> C, E, W, N, S, NE, NW, SE, SW;
+  U2<T> bN, bS, bNE, bNW, bSE, bSW;
+};
+
+// The derivatives of the penalty source, and four more for Appendix B's
+template <typename T>
+struct Derivs {
+  T rux_x, ruy_y, ux_x, uy_y, uy_x, ux_y, mux_x, muy_y;  // Eq. (20)
+  T ruy_x, muy_x, rux_y, mux_y;                          // Eq. (B3)
+};
+
+// The derivatives at a node by Eq. (10).  u2 gives the U2 record of the
+// centre (0), the east (1) and the west (3) node, for solid neighbours and
+// the Appendix B penalty.
+template <int FEAT, typename T, typename F2>
+__device__ __forceinline__ void derivs_of(VelAround<T>& v, const RowState<T>& rC, const StepPhys<T>& ph,
+                                          F2&& u2, Derivs<T>& d) {
+  const U4<T> aC = v.C;
+  if constexpr ((FEAT & FEAT_MASK) != 0) {
+    // solid neighbour: the centre's velocity-like fields, negated
+    const unsigned nb = rC.nb;
+    const U2<T> bC = u2(0);
+    U4<T> ga;
+    ga.ux = -aC.ux; ga.uy = -aC.uy; ga.mux = -aC.mux; ga.rux = -aC.rux;
+    U2<T> gb;
+    gb.muy = -bC.muy; gb.ruy = -bC.ruy;
+    auto sel4 = [&](U4<T>& w, int i) {
+      const bool s2 = solid_bit(nb, i);
+      w.ux = s2 ? ga.ux : w.ux; w.uy = s2 ? ga.uy : w.uy;
+      w.mux = s2 ? ga.mux : w.mux; w.rux = s2 ? ga.rux : w.rux;
+    };
+    auto sel2 = [&](U2<T>& w, int i) {
+      const bool s2 = solid_bit(nb, i);
+      w.muy = s2 ? gb.muy : w.muy; w.ruy = s2 ? gb.ruy : w.ruy;
+    };
+    sel4(v.E, 1); sel4(v.N, 2); sel4(v.W, 3); sel4(v.S, 4);
+    sel4(v.NE, 5); sel4(v.NW, 6); sel4(v.SW, 7); sel4(v.SE, 8);
+    sel2(v.bN, 2); sel2(v.bS, 4); sel2(v.bNE, 5); sel2(v.bNW, 6); sel2(v.bSW, 7); sel2(v.bSE, 8);
+  }
+  // the eight derivatives of Eq. (20), each by Eq. (10)
+  d.rux_x = stencil_dx(v.E.rux, v.W.rux, v.NE.rux, v.SE.rux, v.NW.rux, v.SW.rux);
+  d.ruy_y = stencil_dy(v.bN.ruy, v.bS.ruy, v.bNE.ruy, v.bNW.ruy, v.bSE.ruy, v.bSW.ruy);
+  d.ux_x = stencil_dx(v.E.ux, v.W.ux, v.NE.ux, v.SE.ux, v.NW.ux, v.SW.ux);
+  d.uy_y = stencil_dy(v.N.uy, v.S.uy, v.NE.uy, v.NW.uy, v.SE.uy, v.SW.uy);
+  d.uy_x = stencil_dx(v.E.uy, v.W.uy, v.NE.uy, v.SE.uy, v.NW.uy, v.SW.uy);
+  d.ux_y = stencil_dy(v.N.ux, v.S.ux, v.NE.ux, v.NW.ux, v.SE.ux, v.SW.ux);
+  d.mux_x = stencil_dx(v.E.mux, v.W.mux, v.NE.mux, v.SE.mux, v.NW.mux, v.SW.mux);
+  d.muy_y = stencil_dy(v.bN.muy, v.bS.muy, v.bNE.muy, v.bNW.muy, v.bSE.muy, v.bSW.muy);
+  if ((FEAT & FEAT_SCHEME) && ph.eq2) {
+    U2<T> bE = u2(1), bW = u2(3);
+    if constexpr ((FEAT & FEAT_MASK) != 0) {
+      const U2<T> bC = u2(0);
+      const bool sE = solid_bit(rC.nb, 1), sW = solid_bit(rC.nb, 3);
+      bE.muy = sE ? -bC.muy : bE.muy; bE.ruy = sE ? -bC.ruy : bE.ruy;
+      bW.muy = sW ? -bC.muy : bW.muy; bW.ruy = sW ? -bC.ruy : bW.ruy;
+    }
+    d.ruy_x = stencil_dx(bE.ruy, bW.ruy, v.bNE.ruy, v.bSE.ruy, v.bNW.ruy, v.bSW.ruy);
+    d.muy_x = stencil_dx(bE.muy, bW.muy, v.bNE.muy, v.bSE.muy, v.bNW.muy, v.bSW.muy);
+    d.rux_y = stencil_dy(v.N.rux, v.S.rux, v.NE.rux, v.NW.rux, v.SE.rux, v.SW.rux);
+    d.mux_y = stencil_dy(v.N.mux, v.S.mux, v.NE.mux, v.NW.mux, v.SE.mux, v.SW.mux);
+  }
+}
+
+// Stage C of a node from the derivatives d and the velocity (ux, uy): the
+// penalty source, collision (Eq. 16-19) and back-transform (Eq. A1) into the
+// deviations o9.
+template <int FEAT, typename T>
+__device__ __forceinline__ void collide_of(const Derivs<T>& d, const RowState<T>& rC, T ux, T uy, T Fx, T Fy,
+                                           const StepPhys<T>& ph, T (&o9)[9]) {
+  const T phi = rC.phi;
+  const T rho = ph.rho0 + rC.drho, kappa = ph.kappa;
+  const T X = kappa * recip(phi);
+  const bool eq2 = (FEAT & FEAT_SCHEME) && ph.eq2;
+  const T kmp = kappa - (((FEAT & FEAT_SCHEME) && ph.model_b) ? T(1) : phi);
+
+  // penalty source (Eq. 20, or B3 for the second-order equilibrium);
+  // d.t phi = phi(t+1) - phi(t), zero when static
+  T Ca, Cb, Cc;
+  if (eq2) {
+    Ca = T(-2) * kappa * (d.rux_x + d.ruy_y) + T(2) * kmp * rho * (d.ux_x + d.uy_y) +
+         (T(4) - T(2) * X) * (d.mux_x + d.muy_y);
+    Cb = T(-2.0 / 3.0) * kappa * (d.rux_x - d.ruy_y) +
+         T(2.0 / 3.0) * kmp * rho * (d.ux_x - d.uy_y) + T(2.0 / 3.0) * (d.mux_x - d.muy_y);
+    Cc = -T(1.0 / 3.0) * kappa * (d.ruy_x + d.rux_y) + T(1.0 / 3.0) * kmp * rho * (d.uy_x + d.ux_y) +
+         T(1.0 / 3.0) * (d.muy_x + d.mux_y);
+  } else {
+    Ca = -kappa * (d.rux_x + d.ruy_y) + T(2) * kmp * rho * (d.ux_x + d.uy_y) +
+         (T(3) - T(2) * X) * (d.mux_x + d.muy_y);
+    Cb = -kappa * (d.rux_x - d.ruy_y) + T(2.0 / 3.0) * kmp * rho * (d.ux_x - d.uy_y) +
+         (d.mux_x - d.muy_y);
+    Cc = T(1.0 / 3.0) * kmp * rho * (d.uy_x + d.ux_y);
+  }
+  if (FEAT & FEAT_DYNPHI) Ca -= T(2) * X * rho * rC.dphi;
+
+  // equilibria (Eq. 18) minus those of the rest state
+  const T m0 = phi * ph.rho0 + rC.dm0;  // phi rho
+  const T drho = rC.drho;
+  const T uu = ux * ux + uy * uy;
+  const T eq_e = (T(2) * kappa - T(4) * phi) * drho + T(3) * m0 * uu;
+  const T eq_ep = (T(4) * phi - T(3) * kappa) * drho - T(3) * m0 * uu;
+  const T qfac = eq2 ? -m0 : (kappa - T(2) * phi) * rho;  // phi rho (X - 2), or -phi rho (B2)
+  const T eq_qx = qfac * ux, eq_qy = qfac * uy;
+  const T eq_pxx = m0 * (ux * ux - uy * uy);
+  const T eq_pxy = m0 * (ux * uy);
+
+  // force moments (Eq. 19)
+  const T uF = ux * Fx + uy * Fy;
+  const T S1 = T(6) * uF;
+  const T S7 = T(2) * (ux * Fx - uy * Fy);
+  const T S8 = ux * Fy + uy * Fx;
+
+  // relaxation (Eq. 16); conserved moments: m0+ = m0, j+ = j + F
+  const T he = T(1) - T(0.5) * ph.s_e, hep = T(1) - T(0.5) * ph.s_eps;
+  const T hq = T(1) - T(0.5) * ph.s_q, hn = T(1) - T(0.5) * ph.s_nu;
+  const T pe = rC.me - ph.s_e * (rC.me - eq_e) + he * (S1 + Ca);
+  const T pep = rC.mep - ph.s_eps * (rC.mep - eq_ep) - hep * S1;
+  const T pqx = rC.mqx - ph.s_q * (rC.mqx - eq_qx) - hq * Fx;
+  const T pqy = rC.mqy - ph.s_q * (rC.mqy - eq_qy) - hq * Fy;
+  const T ppxx = rC.mpxx - ph.s_nu * (rC.mpxx - eq_pxx) + hn * (S7 + Cb);
+  const T ppxy = rC.mpxy - ph.s_nu * (rC.mpxy - eq_pxy) + hn * (S8 + Cc);
+  const T pm0 = rC.dm0;
+  const T pjx = rC.jx + Fx;
+  const T pjy = rC.jy + Fy;
+
+  // back-transform f+ = M^-1 m+ (Eq. A1)
+  const T a = (T(4) * pm0 - pe - T(2) * pep) * T(1.0 / 36.0);
+  const T b = (T(4) * pm0 + T(2) * pe + pep) * T(1.0 / 36.0);
+  const T X1 = (pjx - pqx) * T(1.0 / 6.0), Y1 = (pjy - pqy) * T(1.0 / 6.0);
+  const T X2 = (T(2) * pjx + pqx) * T(1.0 / 12.0), Y2 = (T(2) * pjy + pqy) * T(1.0 / 12.0);
+  const T Pd = ppxx * T(0.25), Qd = ppxy * T(0.25);
+  o9[0] = (pm0 - pe + pep) * T(1.0 / 9.0);
+  o9[1] = a + X1 + Pd;
+  o9[2] = a + Y1 - Pd;
+  o9[3] = a - X1 + Pd;
+  o9[4] = a - Y1 - Pd;
+  o9[5] = b + X2 + Y2 + Qd;
+  o9[6] = b - X2 + Y2 - Qd;
+  o9[7] = b - X2 - Y2 + Qd;
+  o9[8] = b + X2 - Y2 - Qd;
+  if constexpr ((FEAT & FEAT_MASK) != 0) {  // solid node: keep the rest state
+    if (solid_bit(rC.nb, 0)) {
+#pragma unroll
+      for (int i = 0; i < 9; ++i) o9[i] = T(0);
+    }
+  }
+}
+
 // S: storage type of populations (double, float, _Float16)
 // T: arithmetic type (double, float)
 // SHIFT: memory holds deviations g (scaled by ph.scale in half storage) instead of f
@@ -305,7 +565,6 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
   const int nit = (y1 - y0) + 4;
 
   const T kappa = ph.kappa, rho0 = ph.rho0;
-  const T third = T(1.0 / 3.0);
   // loop-invariant per-lane byte offsets of the own and neighbour columns
   const unsigned xcb = unsigned(c) * SB, xmb = unsigned(cm) * SB, xpb = unsigned(cp) * SB;
   const unsigned xcT = unsigned(c) * TB;
@@ -395,17 +654,7 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
     if (rowA && live) {
       const T phi = phi_in;
       T q[9];
-      if (SHIFT) {  // only half storage carries a scale (2^-e)
-#pragma unroll
-        for (int i = 0; i < 9; ++i)
-          q[i] = sizeof(S) == 2 ? static_cast<T>(f[i]) * ph.inv_scale : static_cast<T>(f[i]);
-      } else {
-        q[0] = static_cast<T>(f[0]) - (phi * rho0 - ph.rest0_k);
-#pragma unroll
-        for (int i = 1; i < 5; ++i) q[i] = static_cast<T>(f[i]) - ph.rest_axis;
-#pragma unroll
-        for (int i = 5; i < 9; ++i) q[i] = static_cast<T>(f[i]) - ph.rest_diag;
-      }
+      deviations<S, T, SHIFT>(f, phi, ph, q);
       if constexpr (WALLS && (FEAT & FEAT_SCHEME) != 0) {
         // moving walls: a population that crossed the wall returns less the
         // odd part of the equilibrium at the wall velocity, which for the
@@ -423,18 +672,7 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
           q[8] += c1;
         }
       }
-      // rows of M (Eq. A1) applied to the deviations
-      const T sa = (q[1] + q[2]) + (q[3] + q[4]);
-      const T sd = (q[5] + q[6]) + (q[7] + q[8]);
-      rA.dm0 = q[0] + (sa + sd);
-      rA.jx = (q[1] - q[3]) + ((q[5] - q[6]) + (q[8] - q[7]));
-      rA.jy = (q[2] - q[4]) + ((q[5] + q[6]) - (q[7] + q[8]));
-      rA.me = T(-4) * q[0] - sa + T(2) * sd;
-      rA.mep = T(4) * q[0] - T(2) * sa + sd;
-      rA.mqx = T(-2) * (q[1] - q[3]) + ((q[5] - q[6]) + (q[8] - q[7]));
-      rA.mqy = T(-2) * (q[2] - q[4]) + ((q[5] + q[6]) - (q[7] + q[8]));
-      rA.mpxx = (q[1] + q[3]) - (q[2] + q[4]);
-      rA.mpxy = (q[5] + q[7]) - (q[6] + q[8]);
+      moments_of(q, rA);
       rA.phi = phi;
       rA.beta = beta_in;
       rA.dphi = (FEAT & FEAT_DYNPHI) ? phin_in - phi : T(0);
@@ -456,55 +694,21 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
     const bool rowB = (yb >= y0 - 1) && (WALLS ? (yb >= 0 && yb < ny) : true);
     if (rowB && ulane) {
       const int sc = slot4(yb), ss = slot4(yb - 1), sn = slot4(yb + 1);
-      T rE = s_rho[sc][tr], rW = s_rho[sc][tl];
-      T rN = s_rho[sn][tc], rS = s_rho[ss][tc];
-      T rNE = s_rho[sn][tr], rNW = s_rho[sn][tl];
-      T rSE = s_rho[ss][tr], rSW = s_rho[ss][tl];
-      if constexpr ((FEAT & FEAT_MASK) != 0) {  // solid neighbour: centre value
-        const unsigned nb = rB.nb;
-        const T rc = rB.drho;
-        rE = solid_bit(nb, 1) ? rc : rE;
-        rN = solid_bit(nb, 2) ? rc : rN;
-        rW = solid_bit(nb, 3) ? rc : rW;
-        rS = solid_bit(nb, 4) ? rc : rS;
-        rNE = solid_bit(nb, 5) ? rc : rNE;
-        rNW = solid_bit(nb, 6) ? rc : rNW;
-        rSW = solid_bit(nb, 7) ? rc : rSW;
-        rSE = solid_bit(nb, 8) ? rc : rSE;
-      }
-      const T grx = stencil_dx(rE, rW, rNE, rSE, rNW, rSW);
-      const T gry = stencil_dy(rN, rS, rNE, rNW, rSE, rSW);
-      const T phi = rB.phi;
-      const T kf = ((FEAT & FEAT_SCHEME) && ph.model_b) ? T(1) : phi;
-      const T kp = (kappa - kf) * third;  // Eq. (13); kappa - 1 for model B
-      const T sg = ph.scale_by_phi ? phi : T(1);
-      T Fx = kp * grx + sg * ph.gx;
-      T Fy = kp * gry + sg * ph.gy;
+      RhoAround<T> n;
+      n.E = s_rho[sc][tr]; n.W = s_rho[sc][tl];
+      n.N = s_rho[sn][tc]; n.S = s_rho[ss][tc];
+      n.NE = s_rho[sn][tr]; n.NW = s_rho[sn][tl];
+      n.SE = s_rho[ss][tr]; n.SW = s_rho[ss][tl];
+      T ffx = T(0), ffy = T(0);
       if (FEAT & FEAT_FORCE) {
         const unsigned ro = unsigned(WALLS ? yb : wrap_index(yb, ny)) * unsigned(pitch) * TB;
-        Fx += bload<T>(fxr, xcT, ro);
-        Fy += bload<T>(fyr, xcT, ro);
+        ffx = bload<T>(fxr, xcT, ro);
+        ffy = bload<T>(fyr, xcT, ro);
       }
-      const T m0 = phi * rho0 + rB.dm0;
-      T ux, uy;
-      if (FEAT & FEAT_DRAG) {
-        // F = F' - phi beta (u - u_s) with u = (j + F/2)/m0: solved for u
-        const T d = phi * rB.beta;
-        const T inv = recip(m0 + T(0.5) * d);
-        ux = (rB.jx + T(0.5) * (Fx + d * ph.usx)) * inv;
-        uy = (rB.jy + T(0.5) * (Fy + d * ph.usy)) * inv;
-        Fx -= d * (ux - ph.usx);
-        Fy -= d * (uy - ph.usy);
-      } else {
-        const T inv_m0 = recip(m0);
-        ux = (rB.jx + T(0.5) * Fx) * inv_m0;
-        uy = (rB.jy + T(0.5) * Fy) * inv_m0;
-      }
-      const T rho = rho0 + rB.drho;
       U4<T> a;
       U2<T> b;
-      a.ux = ux; a.uy = uy; a.mux = m0 * ux; a.rux = rho * ux;
-      b.muy = m0 * uy; b.ruy = rho * uy;
+      T m0, rho;
+      velocity_of<FEAT>(n, rB, ffx, ffy, ph, a, b, bNew[0], bNew[1], m0, rho);
       if constexpr (NEE) {
         // velocity row: the wall velocity, with the density of the fluid row
         // next to it (row 1 is this iteration's stage-A row, row ny - 2 its
@@ -513,7 +717,7 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
         if (lo || hi) {
           const T rf = rho0 + (lo ? rA.drho : rC.drho);
           const T uw = lo ? ph.un_lo : ph.un_hi;
-          a.ux = uw; a.uy = T(0); a.mux = phi * rf * uw; a.rux = rf * uw;
+          a.ux = uw; a.uy = T(0); a.mux = rB.phi * rf * uw; a.rux = rf * uw;
           b.muy = T(0); b.ruy = T(0);
         }
       }
@@ -542,8 +746,6 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
         s_u4[sg2][t] = am;
         s_u2[sg2][t] = bm;
       }
-      bNew[0] = Fx;
-      bNew[1] = Fy;
     }
     __syncthreads();
     if (sizeof(S) != 4) __builtin_amdgcn_s_setprio(0);  // stage C after them
@@ -552,152 +754,24 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
     const int yo = yn - 2;
     if (yo >= y0 && olane) {
       const int uo = slot4(yo), us = slot4(yo - 1), un = slot4(yo + 1);
-      const U4<T> aC = s_u4[uo][tc];
-      U4<T> aE = s_u4[uo][tr], aW = s_u4[uo][tl];
-      U4<T> aN = s_u4[un][tc], aS = s_u4[us][tc];
-      U4<T> aNE = s_u4[un][tr], aNW = s_u4[un][tl];
-      U4<T> aSE = s_u4[us][tr], aSW = s_u4[us][tl];
-      U2<T> bN = s_u2[un][tc], bS = s_u2[us][tc];
-      U2<T> bNE = s_u2[un][tr], bNW = s_u2[un][tl];
-      U2<T> bSE = s_u2[us][tr], bSW = s_u2[us][tl];
-      if constexpr ((FEAT & FEAT_MASK) != 0) {
-        // solid neighbour: the centre's velocity-like fields, negated
-        const unsigned nb = rC.nb;
-        const U2<T> bC = s_u2[uo][tc];
-        U4<T> ga;
-        ga.ux = -aC.ux; ga.uy = -aC.uy; ga.mux = -aC.mux; ga.rux = -aC.rux;
-        U2<T> gb;
-        gb.muy = -bC.muy; gb.ruy = -bC.ruy;
-        auto sel4 = [&](U4<T>& v, int i) {
-          const bool s2 = solid_bit(nb, i);
-          v.ux = s2 ? ga.ux : v.ux; v.uy = s2 ? ga.uy : v.uy;
-          v.mux = s2 ? ga.mux : v.mux; v.rux = s2 ? ga.rux : v.rux;
-        };
-        auto sel2 = [&](U2<T>& v, int i) {
-          const bool s2 = solid_bit(nb, i);
-          v.muy = s2 ? gb.muy : v.muy; v.ruy = s2 ? gb.ruy : v.ruy;
-        };
-        sel4(aE, 1); sel4(aN, 2); sel4(aW, 3); sel4(aS, 4);
-        sel4(aNE, 5); sel4(aNW, 6); sel4(aSW, 7); sel4(aSE, 8);
-        sel2(bN, 2); sel2(bS, 4); sel2(bNE, 5); sel2(bNW, 6); sel2(bSW, 7); sel2(bSE, 8);
-      }
-
-      // the eight derivatives of Eq. (20), each by Eq. (10)
-      const T d_rux_x = stencil_dx(aE.rux, aW.rux, aNE.rux, aSE.rux, aNW.rux, aSW.rux);
-      const T d_ruy_y = stencil_dy(bN.ruy, bS.ruy, bNE.ruy, bNW.ruy, bSE.ruy, bSW.ruy);
-      const T d_ux_x = stencil_dx(aE.ux, aW.ux, aNE.ux, aSE.ux, aNW.ux, aSW.ux);
-      const T d_uy_y = stencil_dy(aN.uy, aS.uy, aNE.uy, aNW.uy, aSE.uy, aSW.uy);
-      const T d_uy_x = stencil_dx(aE.uy, aW.uy, aNE.uy, aSE.uy, aNW.uy, aSW.uy);
-      const T d_ux_y = stencil_dy(aN.ux, aS.ux, aNE.ux, aNW.ux, aSE.ux, aSW.ux);
-      const T d_mux_x = stencil_dx(aE.mux, aW.mux, aNE.mux, aSE.mux, aNW.mux, aSW.mux);
-      const T d_muy_y = stencil_dy(bN.muy, bS.muy, bNE.muy, bNW.muy, bSE.muy, bSW.muy);
-
-      const T phi = rC.phi;
-      const T rho = rho0 + rC.drho;
-      const T X = kappa * recip(phi);
-      const bool eq2 = (FEAT & FEAT_SCHEME) && ph.eq2;
-      const T kmp = kappa - (((FEAT & FEAT_SCHEME) && ph.model_b) ? T(1) : phi);
-      const T ux = aC.ux, uy = aC.uy, Fx = bOld[0], Fy = bOld[1];
-
-      // penalty source (Eq. 20, or B3 for the second-order equilibrium);
-      // d_t phi = phi(t+1) - phi(t), zero when static
-      T Ca, Cb, Cc;
-      if (eq2) {
-        U2<T> bE = s_u2[uo][tr], bW = s_u2[uo][tl];
-        if constexpr ((FEAT & FEAT_MASK) != 0) {
-          const U2<T> bC = s_u2[uo][tc];
-          const bool sE = solid_bit(rC.nb, 1), sW = solid_bit(rC.nb, 3);
-          bE.muy = sE ? -bC.muy : bE.muy; bE.ruy = sE ? -bC.ruy : bE.ruy;
-          bW.muy = sW ? -bC.muy : bW.muy; bW.ruy = sW ? -bC.ruy : bW.ruy;
-        }
-        const T d_ruy_x = stencil_dx(bE.ruy, bW.ruy, bNE.ruy, bSE.ruy, bNW.ruy, bSW.ruy);
-        const T d_muy_x = stencil_dx(bE.muy, bW.muy, bNE.muy, bSE.muy, bNW.muy, bSW.muy);
-        const T d_rux_y = stencil_dy(aN.rux, aS.rux, aNE.rux, aNW.rux, aSE.rux, aSW.rux);
-        const T d_mux_y = stencil_dy(aN.mux, aS.mux, aNE.mux, aNW.mux, aSE.mux, aSW.mux);
-        Ca = T(-2) * kappa * (d_rux_x + d_ruy_y) + T(2) * kmp * rho * (d_ux_x + d_uy_y) +
-             (T(4) - T(2) * X) * (d_mux_x + d_muy_y);
-        Cb = T(-2.0 / 3.0) * kappa * (d_rux_x - d_ruy_y) +
-             T(2.0 / 3.0) * kmp * rho * (d_ux_x - d_uy_y) + T(2.0 / 3.0) * (d_mux_x - d_muy_y);
-        Cc = -third * kappa * (d_ruy_x + d_rux_y) + third * kmp * rho * (d_uy_x + d_ux_y) +
-             third * (d_muy_x + d_mux_y);
-      } else {
-        Ca = -kappa * (d_rux_x + d_ruy_y) + T(2) * kmp * rho * (d_ux_x + d_uy_y) +
-             (T(3) - T(2) * X) * (d_mux_x + d_muy_y);
-        Cb = -kappa * (d_rux_x - d_ruy_y) + T(2.0 / 3.0) * kmp * rho * (d_ux_x - d_uy_y) +
-             (d_mux_x - d_muy_y);
-        Cc = third * kmp * rho * (d_uy_x + d_ux_y);
-      }
-      if (FEAT & FEAT_DYNPHI) Ca -= T(2) * X * rho * rC.dphi;
-
-      // equilibria (Eq. 18) minus those of the rest state
-      const T m0 = phi * rho0 + rC.dm0;  // phi rho
-      const T drho = rC.drho;
-      const T uu = ux * ux + uy * uy;
-      const T eq_e = (T(2) * kappa - T(4) * phi) * drho + T(3) * m0 * uu;
-      const T eq_ep = (T(4) * phi - T(3) * kappa) * drho - T(3) * m0 * uu;
-      const T qfac = eq2 ? -m0 : (kappa - T(2) * phi) * rho;  // phi rho (X - 2), or -phi rho (B2)
-      const T eq_qx = qfac * ux, eq_qy = qfac * uy;
-      const T eq_pxx = m0 * (ux * ux - uy * uy);
-      const T eq_pxy = m0 * (ux * uy);
-
-      // force moments (Eq. 19)
-      const T uF = ux * Fx + uy * Fy;
-      const T S1 = T(6) * uF;
-      const T S7 = T(2) * (ux * Fx - uy * Fy);
-      const T S8 = ux * Fy + uy * Fx;
-
-      // relaxation (Eq. 16); conserved moments: m0+ = m0, j+ = j + F
-      const T he = T(1) - T(0.5) * ph.s_e, hep = T(1) - T(0.5) * ph.s_eps;
-      const T hq = T(1) - T(0.5) * ph.s_q, hn = T(1) - T(0.5) * ph.s_nu;
-      const T pe = rC.me - ph.s_e * (rC.me - eq_e) + he * (S1 + Ca);
-      const T pep = rC.mep - ph.s_eps * (rC.mep - eq_ep) - hep * S1;
-      const T pqx = rC.mqx - ph.s_q * (rC.mqx - eq_qx) - hq * Fx;
-      const T pqy = rC.mqy - ph.s_q * (rC.mqy - eq_qy) - hq * Fy;
-      const T ppxx = rC.mpxx - ph.s_nu * (rC.mpxx - eq_pxx) + hn * (S7 + Cb);
-      const T ppxy = rC.mpxy - ph.s_nu * (rC.mpxy - eq_pxy) + hn * (S8 + Cc);
-      const T pm0 = rC.dm0;
-      const T pjx = rC.jx + Fx;
-      const T pjy = rC.jy + Fy;
-
-      // back-transform f+ = M^-1 m+ (Eq. A1)
-      const T a = (T(4) * pm0 - pe - T(2) * pep) * T(1.0 / 36.0);
-      const T b = (T(4) * pm0 + T(2) * pe + pep) * T(1.0 / 36.0);
-      const T X1 = (pjx - pqx) * T(1.0 / 6.0), Y1 = (pjy - pqy) * T(1.0 / 6.0);
-      const T X2 = (T(2) * pjx + pqx) * T(1.0 / 12.0), Y2 = (T(2) * pjy + pqy) * T(1.0 / 12.0);
-      const T Pd = ppxx * T(0.25), Qd = ppxy * T(0.25);
+      VelAround<T> v;
+      v.C = s_u4[uo][tc];
+      v.E = s_u4[uo][tr]; v.W = s_u4[uo][tl];
+      v.N = s_u4[un][tc]; v.S = s_u4[us][tc];
+      v.NE = s_u4[un][tr]; v.NW = s_u4[un][tl];
+      v.SE = s_u4[us][tr]; v.SW = s_u4[us][tl];
+      v.bN = s_u2[un][tc]; v.bS = s_u2[us][tc];
+      v.bNE = s_u2[un][tr]; v.bNW = s_u2[un][tl];
+      v.bSE = s_u2[us][tr]; v.bSW = s_u2[us][tl];
       T o9[9];
-      o9[0] = (pm0 - pe + pep) * T(1.0 / 9.0);
-      o9[1] = a + X1 + Pd;
-      o9[2] = a + Y1 - Pd;
-      o9[3] = a - X1 + Pd;
-      o9[4] = a - Y1 - Pd;
-      o9[5] = b + X2 + Y2 + Qd;
-      o9[6] = b - X2 + Y2 - Qd;
-      o9[7] = b - X2 - Y2 + Qd;
-      o9[8] = b + X2 - Y2 - Qd;
-      if constexpr ((FEAT & FEAT_MASK) != 0) {  // solid node: keep the rest state
-        if (solid_bit(rC.nb, 0)) {
-#pragma unroll
-          for (int i = 0; i < 9; ++i) o9[i] = T(0);
-        }
-      }
-      // Store deviations o (rest state of void fraction ph_n) on row r.
-      // Shifted storage holds deviations from the rest state of the void
-      // fraction of the time the next pull runs at: rest_0 changes by
-      // rho0 d_t phi when phi moves (dph_n).
+      Derivs<T> d;
+      derivs_of<FEAT>(v, rC, ph, [&](int i) { return s_u2[uo][i == 0 ? tc : (i == 1 ? tr : tl)]; }, d);
+      collide_of<FEAT>(d, rC, v.C.ux, v.C.uy, bOld[0], bOld[1], ph, o9);
       auto store_row = [&](T (&o)[9], T ph_n, T dph_n, int r) {
-        if (SHIFT && (FEAT & FEAT_DYNPHI)) o[0] -= rho0 * dph_n;
-        if (SHIFT) {
+        S sv[9];
+        stored<S, T, SHIFT, FEAT>(o, ph_n, dph_n, ph, sv);
 #pragma unroll
-          for (int i = 0; i < 9; ++i)
-            bstore(static_cast<S>(sizeof(S) == 2 ? o[i] * ph.scale : o[i]), dstr, xcb, poff(i, r));
-        } else {
-          bstore(static_cast<S>(o[0] + (ph_n * rho0 - ph.rest0_k)), dstr, xcb, poff(0, r));
-#pragma unroll
-          for (int i = 1; i < 5; ++i) bstore(static_cast<S>(o[i] + ph.rest_axis), dstr, xcb, poff(i, r));
-#pragma unroll
-          for (int i = 5; i < 9; ++i) bstore(static_cast<S>(o[i] + ph.rest_diag), dstr, xcb, poff(i, r));
-        }
+        for (int i = 0; i < 9; ++i) bstore(sv[i], dstr, xcb, poff(i, r));
       };
 
       if constexpr (NEE) {
@@ -706,6 +780,8 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
         // also sets that row's post-collision state,
         //   f+(x_b) = f^eq(phi_b, rho_f, u_w) + f+(x_f) - f^eq(phi_f, rho_f, u_f),
         // here on deviations; the velocity row itself stores nothing.
+        const T phi = rC.phi, drho = rC.drho, rho = rho0 + drho, ux = v.C.ux, uy = v.C.uy;
+        const bool eq2 = ph.eq2;
         auto vel_row = [&](int rb, T uw) {
           const unsigned ro = unsigned(rb) * unsigned(pitch) * TB;
           const T phb = bload<T>(phir, xcT, ro);
@@ -726,7 +802,7 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
         if (ph.nee_hi && yo == ny - 2) vel_row(ny - 1, ph.un_hi);
         if ((ph.nee_lo && yo == 0) || (ph.nee_hi && yo == ny - 1)) return;
       }
-      store_row(o9, phi, rC.dphi, yo);
+      store_row(o9, rC.phi, rC.dphi, yo);
     }
   };
 

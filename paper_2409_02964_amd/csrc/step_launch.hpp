@@ -10,12 +10,18 @@
 
 #include "step2_kernel.hpp"
 #include "step_kernel.hpp"
+#include "tile_kernel.hpp"
 
 namespace vanse_dev {
 
 // One lattice: `blocks` workgroups of NT lanes over the tiles of g.
 template <typename S, typename T, bool SHIFT, bool WALLS, int FEAT, int NT>
 void launch_step_nt(const StepGeom& g, const StepPhys<T>& ph, int blocks, hipStream_t st);
+
+// One small lattice, `steps` time steps per launch of the tile kernel: one
+// workgroup per tile of g (g.strips tiles a row, each tile_out() nodes a side)
+template <typename S, typename T, bool SHIFT, int FEAT>
+void launch_tile(const StepGeom& g, const StepPhys<T>& ph, int walls, int steps, int blocks, hipStream_t st);
 
 // One lattice, two time steps per launch: `blocks` workgroups of two halves
 // of step2_nt_of(sizeof(T), FEAT) lanes (FEAT: any of the force field, the

@@ -531,6 +531,91 @@ int run_fused_pairs(vanse_lattice* h, int64_t pairs, hipStream_t st) {
   return VANSE_OK;
 }
 
+// The instance of the tile kernel that steps a lattice, or -1: the plain step
+// with any of the force field, the drag, solid nodes and walls in x (those
+// with an absent flag plane, which reads as zero).
+int tile_inst(const vanse_lattice* h) {
+  const int f = feat_of(h);
+  if (h->d.dynamic_phi || (f & FEAT_SCHEME)) return -1;
+  if (f & FEAT_MASK) return (f & (FEAT_FORCE | FEAT_DRAG)) ? (FEAT_MASK | FEAT_FORCE | FEAT_DRAG) : FEAT_MASK;
+  return f;
+}
+
+long long tile_blocks(const vanse_lattice* h, int steps) {
+  const int ox = tile_out(TILE_X, steps), oy = tile_out(tile_y(arith_bytes(h)), steps);
+  return (long long)((h->d.nx + ox - 1) / ox) * ((h->d.ny + oy - 1) / oy);
+}
+
+// Steps per launch of the tile kernel, or 0 for the row sweep (which also
+// serves a launch shape that the caller chose).  As many as leave every CU at
+// most one tile (one workgroup fills a CU's registers), up to four: more
+// steps share a launch, but their tiles output less and recompute more.
+// Where two steps need more than one round of tiles, they still win while the
+// rounds are few -- the line lies where both sides measured alike, from 512 x
+// 512 and 1003 x 777 nodes (us per step, sweep against tiles): FP32 10.8/9.6 at
+// 576 tiles, 18.5/21.8 at 1656; FP64 16.7/14.3 at 888, 27.3/34.6 at 2576; walls
+// in x with a force field or drag, whose sweep runs three waves per SIMD and
+// carries a moving phi's planes, FP16 29.4/24.5 at 1656.
+int tile_steps(const vanse_lattice* h) {
+  if (!h->tiling_default || tile_inst(h) < 0) return 0;
+  const int cus = device_cus();
+  for (int k = 4; k >= 2; --k)
+    if (tile_blocks(h, k) <= cus) return k;
+  const bool slow_sweep = feat_of(h) == (FEAT_MASK | FEAT_MOVING);
+  const int rounds = slow_sweep ? 7 : (h->d.precision == VANSE_F64 ? 4 : 3);
+  return tile_blocks(h, 2) <= (long long)rounds * cus ? 2 : 0;
+}
+
+// n steps with the tile kernel, at most k per launch.  The number of launches
+// is n modulo two, so that a call leaves the state in the same one of the two
+// population buffers as n single steps would (a captured even number of steps
+// can be replayed).
+template <typename S, typename T, bool SHIFT>
+int run_tiles(vanse_lattice* h, int64_t n, int k, hipStream_t st) {
+  if (n <= 0) return VANSE_OK;
+  const StepPhys<T> ph = make_phys<T>(h);
+  StepGeom g{};
+  g.nbr = h->d.has_mask ? h->ws + h->L.nbr : nullptr;
+  g.plane = h->L.plane;
+  g.nx = h->d.nx;
+  g.ny = h->d.ny;
+  g.pitch = h->L.pitch;
+  g.phi = h->ws + h->L.phi;
+  g.fxf = h->d.has_force_field ? h->ws + h->L.fx : nullptr;
+  g.fyf = h->d.has_force_field ? h->ws + h->L.fy : nullptr;
+  g.beta = h->d.has_drag ? h->ws + h->L.beta : nullptr;
+  const int walls = (h->d.bc_y == VANSE_WALL ? 1 : 0) | (h->d.bc_x == VANSE_WALL ? 2 : 0);
+  const int feat = tile_inst(h);
+  int64_t launches = (n + k - 1) / k;
+  if ((launches ^ n) & 1) launches += 1;
+  const int64_t base = n / launches, more = n % launches;
+  for (int64_t s = 0; s < launches; ++s) {
+    const int steps = (int)(base + (s < more ? 1 : 0));
+    const int ox = tile_out(TILE_X, steps);
+    g.strips = (h->d.nx + ox - 1) / ox;
+    const int blocks = (int)tile_blocks(h, steps);
+    g.src = h->ws + h->L.pop[h->cur];
+    g.dst = h->ws + h->L.pop[h->cur ^ 1];
+    switch (feat) {
+      case FEAT_FORCE: launch_tile<S, T, SHIFT, FEAT_FORCE>(g, ph, walls, steps, blocks, st); break;
+      case FEAT_DRAG: launch_tile<S, T, SHIFT, FEAT_DRAG>(g, ph, walls, steps, blocks, st); break;
+      case FEAT_FORCE | FEAT_DRAG:
+        launch_tile<S, T, SHIFT, FEAT_FORCE | FEAT_DRAG>(g, ph, walls, steps, blocks, st);
+        break;
+      case FEAT_MASK: launch_tile<S, T, SHIFT, FEAT_MASK>(g, ph, walls, steps, blocks, st); break;
+      case FEAT_MASK | FEAT_FORCE | FEAT_DRAG:
+        launch_tile<S, T, SHIFT, FEAT_MASK | FEAT_FORCE | FEAT_DRAG>(g, ph, walls, steps, blocks, st);
+        break;
+      default: launch_tile<S, T, SHIFT, 0>(g, ph, walls, steps, blocks, st);
+    }
+    h->cur ^= 1;
+    h->t += steps;
+    if (s == 0) HIP_TRY(hipGetLastError());
+  }
+  HIP_TRY(hipGetLastError());
+  return VANSE_OK;
+}
+
 template <typename S, typename T, bool SHIFT>
 int run_steps(vanse_lattice* h, int64_t n, hipStream_t st) {
   if (h->phin_set && n > 1)
@@ -548,6 +633,9 @@ int run_steps(vanse_lattice* h, int64_t n, hipStream_t st) {
     // void fraction, and the second step's inputs follow it (below)
     h->phin_set = true;
   }
+  // (a single step of several rounds of tiles is no faster than the sweep)
+  if (const int k = tile_steps(h))
+    if (n > 1 || tile_blocks(h, 1) <= device_cus()) return run_tiles<S, T, SHIFT>(h, n, k, st);
   const StepPhys<T> ph = make_phys<T>(h);
   StepGeom g{};
   g.nbr = h->d.has_mask ? h->ws + h->L.nbr : nullptr;
