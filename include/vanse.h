@@ -309,7 +309,9 @@ int vanse_get_tiling(const vanse_lattice *h, int *threads, int *rows,
  * (half that for solid nodes with the drag, a moving phi and the Appendix B
  * equilibrium).  Other
  * lattices keep one step per launch.  rows: rows per workgroup of the
- * two-step kernel (0: one full round of resident workgroups). */
+ * two-step kernel (0: one full round of resident workgroups; lattices too
+ * small to fill the GPU then take up to two pairs per launch of a kernel of
+ * their own, with bitwise the same results). */
 int vanse_set_steps_per_pass(vanse_lattice *h, int steps, int rows);
 /* Whether the two-step launch is in use (*active), and its rows per
  * workgroup and workgroups per launch. */

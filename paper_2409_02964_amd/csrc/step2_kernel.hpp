@@ -320,6 +320,192 @@ __device__ __forceinline__ unsigned flags_of(T v) {
   else return __builtin_bit_cast(unsigned, v);
 }
 
+// ---- the arithmetic of one node in two-step launches ------------------------
+// Shared with the tile kernel, so that both round alike.
+
+// Rows of M (Eq. A1) applied to the deviations q
+template <typename T>
+__device__ __forceinline__ void moments2_of(const T (&q)[9], RowState<T>& r) {
+  const T s13 = q[1] + q[3], s24 = q[2] + q[4];  // (shared with p_xx)
+  const T sa = s13 + s24;
+  const T sd = (q[5] + q[6]) + (q[7] + q[8]);
+  r.dm0 = q[0] + (sa + sd);
+  r.jx = (q[1] - q[3]) + ((q[5] - q[6]) + (q[8] - q[7]));
+  r.jy = (q[2] - q[4]) + ((q[5] + q[6]) - (q[7] + q[8]));
+  r.me = T(-4) * q[0] - sa + T(2) * sd;
+  r.mep = T(4) * q[0] - T(2) * sa + sd;
+  r.mqx = T(-2) * (q[1] - q[3]) + ((q[5] - q[6]) + (q[8] - q[7]));
+  r.mqy = T(-2) * (q[2] - q[4]) + ((q[5] + q[6]) - (q[7] + q[8]));
+  r.mpxx = s13 - s24;
+  r.mpxy = (q[5] + q[7]) - (q[6] + q[8]);
+}
+
+// Stage B of a node from 12 times the gradient of rho (grx, gry): F (Eq. 13
+// and F^B), u (Eq. 7) and its products
+template <int FEAT, typename T>
+__device__ __forceinline__ void velocity2_of(T grx, T gry, const RowState<T>& r, T fex, T fey,
+                                             bool kappa_less_one, const StepPhys<T>& ph, U4<T>& a, U2<T>& b,
+                                             T& Fx, T& Fy) {
+  const T phi = r.phi;
+  const T kp = (ph.kappa - (kappa_less_one ? T(1) : phi)) * T(1.0 / 36.0);  // Eq. (13), with the 1/12
+  const T sg = ph.scale_by_phi ? phi : T(1);
+  Fx = kp * grx + sg * ph.gx;
+  Fy = kp * gry + sg * ph.gy;
+  if (FEAT & FEAT_FORCE) {
+    Fx += fex;
+    Fy += fey;
+  }
+  const T m0 = phi * ph.rho0 + r.dm0;
+  T ux, uy;
+  if (FEAT & FEAT_DRAG) {
+    // F = F' - phi beta (u - u_s) with u = (j + F/2)/m0: solved for u
+    const T d = phi * r.beta;
+    const T inv = recip(m0 + T(0.5) * d);
+    ux = (r.jx + T(0.5) * (Fx + d * ph.usx)) * inv;
+    uy = (r.jy + T(0.5) * (Fy + d * ph.usy)) * inv;
+    Fx -= d * (ux - ph.usx);
+    Fy -= d * (uy - ph.usy);
+  } else {
+    const T inv_m0 = recip(m0);
+    ux = (r.jx + T(0.5) * Fx) * inv_m0;
+    uy = (r.jy + T(0.5) * Fy) * inv_m0;
+  }
+  const T rho = ph.rho0 + r.drho;
+  a.ux = ux; a.uy = uy; a.mux = m0 * ux; a.rux = rho * ux;
+  b.muy = m0 * uy; b.ruy = rho * uy;
+}
+
+// 12 times the derivatives at a node (Derivs) from the separable sums of the
+// rows below (m), of the node (c) and above (n)
+template <int FEAT, typename T>
+__device__ __forceinline__ void derivs2_of(const VelDS<T>& vm, const VelDS<T>& vc, const VelDS<T>& vn,
+                                           Derivs<T>& d) {
+  d.rux_x = T(4) * vc.d_rux + (vm.d_rux + vn.d_rux);
+  d.ux_x = T(4) * vc.d_ux + (vm.d_ux + vn.d_ux);
+  d.uy_x = T(4) * vc.d_uy + (vm.d_uy + vn.d_uy);
+  d.mux_x = T(4) * vc.d_mux + (vm.d_mux + vn.d_mux);
+  d.ruy_y = vn.s_ruy - vm.s_ruy;
+  d.uy_y = vn.s_uy - vm.s_uy;
+  d.ux_y = vn.s_ux - vm.s_ux;
+  d.muy_y = vn.s_muy - vm.s_muy;
+  if constexpr ((FEAT & FEAT_EQ2) != 0) {
+    d.ruy_x = T(4) * vc.d_ruy + (vm.d_ruy + vn.d_ruy);
+    d.muy_x = T(4) * vc.d_muy + (vm.d_muy + vn.d_muy);
+    d.rux_y = vn.s_rux - vm.s_rux;
+    d.mux_y = vn.s_mux - vm.s_mux;
+  }
+}
+
+// Stage C of a node from 12 times the derivatives (d) and the velocity: the
+// penalty source, collision and back-transform into the deviations o9, times
+// the storage scale with `scaled`.  nbC: solid flags.
+template <int FEAT, typename T>
+__device__ __forceinline__ void collide2_of(const Derivs<T>& d, const RowState<T>& rC, unsigned nbC, T ux, T uy,
+                                            T Fx, T Fy, bool kappa_less_one, bool scaled,
+                                            const StepPhys<T>& ph, T (&o9)[9]) {
+  constexpr bool MASK = (FEAT & FEAT_MASK) != 0, DYN = (FEAT & FEAT_DYNPHI) != 0, EQ2 = (FEAT & FEAT_EQ2) != 0;
+  constexpr unsigned BOUNCE = 0x1FEu;  // neighbour bits of the flags
+  const T phi = rC.phi;
+  const T rho = ph.rho0 + rC.drho;
+  const T m0 = phi * ph.rho0 + rC.dm0;
+  const T X = ph.kappa * (MASK ? recip(phi) : rC.rphi);
+  const T kr = (ph.kappa - (kappa_less_one ? T(1) : phi)) * rho;
+
+  // penalty source (Eq. 20), static void fraction; the 1/12 of the
+  // derivatives is folded into the coefficients
+  T Ca, Cb, Cc;
+  if constexpr (EQ2) {
+    // Eq. (B3): twice the kappa and the phi rho u terms of Ca, two
+    // thirds of those of Cb, and Cc with all three kinds of term
+    Ca = T(-2) * ph.k12 * (d.rux_x + d.ruy_y) + (kr * T(1.0 / 6.0)) * (d.ux_x + d.uy_y) +
+         (T(1.0 / 3.0) - X * T(1.0 / 6.0)) * (d.mux_x + d.muy_y);
+    Cb = T(-2.0 / 3.0) * ph.k12 * (d.rux_x - d.ruy_y) + (kr * T(1.0 / 18.0)) * (d.ux_x - d.uy_y) +
+         T(1.0 / 18.0) * (d.mux_x - d.muy_y);
+    Cc = T(-1.0 / 3.0) * ph.k12 * (d.ruy_x + d.rux_y) + (kr * T(1.0 / 36.0)) * (d.uy_x + d.ux_y) +
+         T(1.0 / 36.0) * (d.muy_x + d.mux_y);
+  } else {
+    Ca = -ph.k12 * (d.rux_x + d.ruy_y) + (kr * T(1.0 / 6.0)) * (d.ux_x + d.uy_y) +
+         (T(0.25) - X * T(1.0 / 6.0)) * (d.mux_x + d.muy_y);
+    Cb = -ph.k12 * (d.rux_x - d.ruy_y) + (kr * T(1.0 / 18.0)) * (d.ux_x - d.uy_y) +
+         T(1.0 / 12.0) * (d.mux_x - d.muy_y);
+    Cc = (kr * T(1.0 / 36.0)) * (d.uy_x + d.ux_y);
+  }
+  if (DYN) Ca -= T(2) * X * rho * rC.dphi;  // moving phi (Eq. 20)
+  if constexpr (MASK) {
+    if (wave_any((nbC & BOUNCE) != 0)) {
+      // Solid neighbours stand in with the centre's velocity-like
+      // fields negated: each derivative gains -Kx (or -Ky) times the
+      // centre's rho u, u or (phi rho) u, here gathered into the three
+      // sums (rho u = rho (u), (phi rho) u = m0 (u))
+      const T kx = T(solid_kx(nbC)), ky = T(solid_ky(nbC));
+      const T sp = kx * ux + ky * uy, sm = kx * ux - ky * uy, sc = kx * uy + ky * ux;
+      if constexpr (EQ2) {  // the same with the coefficients of Eq. (B3)
+        Ca -= sp * ((kr * T(1.0 / 6.0) - T(2) * ph.k12 * rho) + (T(1.0 / 3.0) - X * T(1.0 / 6.0)) * m0);
+        Cb -= sm * ((kr * T(1.0 / 18.0) - T(2.0 / 3.0) * ph.k12 * rho) + T(1.0 / 18.0) * m0);
+        Cc -= sc * ((kr * T(1.0 / 36.0) - T(1.0 / 3.0) * ph.k12 * rho) + T(1.0 / 36.0) * m0);
+      } else {
+        Ca -= sp * ((kr * T(1.0 / 6.0) - ph.k12 * rho) + (T(0.25) - X * T(1.0 / 6.0)) * m0);
+        Cb -= sm * ((kr * T(1.0 / 18.0) - ph.k12 * rho) + T(1.0 / 12.0) * m0);
+        Cc -= sc * (kr * T(1.0 / 36.0));
+      }
+    }
+  }
+
+  // equilibria (Eq. 18) minus those of the rest state
+  const T drho = rC.drho;
+  const T uu = ux * ux + uy * uy;
+  const T eq_e = (ph.k2 - T(4) * phi) * drho + T(3) * m0 * uu;
+  const T eq_ep = (T(4) * phi - ph.k3) * drho - T(3) * m0 * uu;
+  const T qfac = EQ2 ? -m0 : (ph.kappa - T(2) * phi) * rho;  // phi rho (X - 2), or -phi rho (B2)
+  const T eq_qx = qfac * ux, eq_qy = qfac * uy;
+  const T eq_pxx = m0 * (ux * ux - uy * uy);
+  const T eq_pxy = m0 * (ux * uy);
+
+  // force moments (Eq. 19)
+  const T uF = ux * Fx + uy * Fy;
+  const T S1 = T(6) * uF;
+  const T S7 = T(2) * (ux * Fx - uy * Fy);
+  const T S8 = ux * Fy + uy * Fx;
+
+  // relaxation (Eq. 16); conserved moments: m0+ = m0, j+ = j + F
+  const T he = ph.he, hep = ph.hep, hq = ph.hq, hn = ph.hn;
+  const T pe = rC.me - ph.s_e * (rC.me - eq_e) + he * (S1 + Ca);
+  const T pep = rC.mep - ph.s_eps * (rC.mep - eq_ep) - hep * S1;
+  const T pqx = rC.mqx - ph.s_q * (rC.mqx - eq_qx) - hq * Fx;
+  const T pqy = rC.mqy - ph.s_q * (rC.mqy - eq_qy) - hq * Fy;
+  const T ppxx = rC.mpxx - ph.s_nu * (rC.mpxx - eq_pxx) + hn * (S7 + Cb);
+  const T ppxy = rC.mpxy - ph.s_nu * (rC.mpxy - eq_pxy) + hn * (S8 + Cc);
+  const T pm0 = rC.dm0;
+  const T pjx = rC.jx + Fx;
+  const T pjy = rC.jy + Fy;
+
+  // back-transform f+ = M^-1 m+ (Eq. A1).  A second step with shifted storage
+  // takes the coefficients times the storage scale (a power of two, so the
+  // products are the scaled values exactly, as a multiply at the store would
+  // give them).
+  const T c36 = scaled ? ph.bt36 : T(1.0 / 36.0), c6 = scaled ? ph.bt6 : T(1.0 / 6.0);
+  const T c12 = scaled ? ph.bt12 : T(1.0 / 12.0), c4 = scaled ? ph.bt4 : T(0.25);
+  const T c9 = scaled ? ph.bt9 : T(1.0 / 9.0);
+  const T a = (T(4) * pm0 - pe - T(2) * pep) * c36;
+  const T b = (T(4) * pm0 + T(2) * pe + pep) * c36;
+  const T X1 = (pjx - pqx) * c6, Y1 = (pjy - pqy) * c6;
+  const T X2 = (T(2) * pjx + pqx) * c12, Y2 = (T(2) * pjy + pqy) * c12;
+  const T Pd = ppxx * c4, Qd = ppxy * c4;
+  o9[0] = (pm0 - pe + pep) * c9;
+  // the rows of M^-1 by their shared pairs: six additions fewer than
+  // summing each row's terms in turn
+  const T aP = a + Pd, aM = a - Pd, bP = b + Qd, bM = b - Qd;
+  const T sXY = X2 + Y2, dXY = X2 - Y2;
+  o9[1] = aP + X1;
+  o9[2] = aM + Y1;
+  o9[3] = aP - X1;
+  o9[4] = aM - Y1;
+  o9[5] = bP + sXY;
+  o9[6] = bM - dXY;
+  o9[7] = bP - sXY;
+  o9[8] = bM + dXY;
+}
+
 // FEAT: the plain step plus any of FEAT_FORCE (a per-node force field added
 // to F^B), FEAT_DRAG (the linear drag, u solved in closed form as in the
 // single step), and FEAT_MASK (solid nodes; no walls in x) or FEAT_DYNPHI
@@ -568,21 +754,10 @@ __device__ inline void step2_tile(
 
     // ---------------- stage A: moments of row yA ----------------
     const bool rowA = (WALLS ? (yA >= 0 && yA < ny) : true) && (half == 0 || yA >= y0 - 2);
-    // rows of M (Eq. A1) applied to the deviations q; formed in each half's
-    // branch so that the two sources of q need not share registers
+    // (formed in each half's branch so that the two sources of q need not
+    // share registers)
     auto moments = [&](const T (&q)[9], T phi) {
-      const T s13 = q[1] + q[3], s24 = q[2] + q[4];  // (shared with p_xx)
-      const T sa = s13 + s24;
-      const T sd = (q[5] + q[6]) + (q[7] + q[8]);
-      rA.dm0 = q[0] + (sa + sd);
-      rA.jx = (q[1] - q[3]) + ((q[5] - q[6]) + (q[8] - q[7]));
-      rA.jy = (q[2] - q[4]) + ((q[5] + q[6]) - (q[7] + q[8]));
-      rA.me = T(-4) * q[0] - sa + T(2) * sd;
-      rA.mep = T(4) * q[0] - T(2) * sa + sd;
-      rA.mqx = T(-2) * (q[1] - q[3]) + ((q[5] - q[6]) + (q[8] - q[7]));
-      rA.mqy = T(-2) * (q[2] - q[4]) + ((q[5] + q[6]) - (q[7] + q[8]));
-      rA.mpxx = s13 - s24;
-      rA.mpxy = (q[5] + q[7]) - (q[6] + q[8]);
+      moments2_of(q, rA);
       rA.phi = phi;
       const T rp = recip(phi);
       if constexpr (!MASK) rA.rphi = rp;  // (recomputed with solid nodes: registers)
@@ -750,43 +925,15 @@ __device__ inline void step2_tile(
             gry += T(solid_ky(nbB)) * rB.drho;
           }
         }
-        const T phi = rB.phi;
-        const T kp = (kappa - (kappa_less_one ? T(1) : phi)) * T(1.0 / 36.0);  // Eq. (13), with the 1/12
-        const T sg = ph.scale_by_phi ? phi : T(1);
-        T Fx = kp * grx + sg * ph.gx;
-        T Fy = kp * gry + sg * ph.gy;
-        if (FORCE) {
-          Fx += fex;
-          Fy += fey;
-        }
-        const T m0 = phi * rho0 + rB.dm0;
-        T ux, uy;
-        if (DRAG) {
-          // F = F' - phi beta (u - u_s) with u = (j + F/2)/m0: solved for u
-          const T d = phi * rB.beta;
-          const T inv = recip(m0 + T(0.5) * d);
-          ux = (rB.jx + T(0.5) * (Fx + d * ph.usx)) * inv;
-          uy = (rB.jy + T(0.5) * (Fy + d * ph.usy)) * inv;
-          Fx -= d * (ux - ph.usx);
-          Fy -= d * (uy - ph.usy);
-        } else {
-          const T inv_m0 = recip(m0);
-          ux = (rB.jx + T(0.5) * Fx) * inv_m0;
-          uy = (rB.jy + T(0.5) * Fy) * inv_m0;
-        }
-        const T rho = rho0 + rB.drho;
         U4<T> a;
         U2<T> b;
-        a.ux = ux; a.uy = uy; a.mux = m0 * ux; a.rux = rho * ux;
-        b.muy = m0 * uy; b.ruy = rho * uy;
+        velocity2_of<FEAT>(grx, gry, rB, fex, fey, kappa_less_one, ph, a, b, bNew[0], bNew[1]);
         if (MASK && solid_bit(fl.hi, 10)) {  // solid node: zero, left out of the sums
           a.ux = a.uy = a.mux = a.rux = T(0);
           b.muy = b.ruy = T(0);
         }
         lds_put(s_u4[t], a);
         lds_put(s_u2[t], b);
-        bNew[0] = Fx;
-        bNew[1] = Fy;
       } else if (WALLS && yb == ny) {  // above the upper wall: row ny - 1, negated
         U4<T> a = lds_get(s_u4[t]);
         U2<T> b = lds_get(s_u2[t]);
@@ -857,123 +1004,12 @@ __device__ inline void step2_tile(
         }
       }
       if (rowC && olane) {
-        // the eight derivatives of Eq. (20), each 12 times its Eq. (10) value
-        const T dx_rux = T(4) * vc.d_rux + (vm.d_rux + vn.d_rux);
-        const T dx_ux = T(4) * vc.d_ux + (vm.d_ux + vn.d_ux);
-        const T dx_uy = T(4) * vc.d_uy + (vm.d_uy + vn.d_uy);
-        const T dx_mux = T(4) * vc.d_mux + (vm.d_mux + vn.d_mux);
-        const T dy_ruy = vn.s_ruy - vm.s_ruy;
-        const T dy_uy = vn.s_uy - vm.s_uy;
-        const T dy_ux = vn.s_ux - vm.s_ux;
-        const T dy_muy = vn.s_muy - vm.s_muy;
-
-        const T phi = rC.phi;
-        const T rho = rho0 + rC.drho;
-        const T m0 = phi * rho0 + rC.dm0;
-        const T X = kappa * (MASK ? recip(phi) : rC.rphi);
-        const T kr = (kappa - (kappa_less_one ? T(1) : phi)) * rho;
-        const T ux = vc.ux, uy = vc.uy, Fx = bOld[0], Fy = bOld[1];
-
-        // penalty source (Eq. 20), static void fraction; the 1/12 of the
-        // derivatives is folded into the coefficients
-        T Ca, Cb, Cc;
-        if constexpr (EQ2) {
-          // Eq. (B3): twice the kappa and the phi rho u terms of Ca, two
-          // thirds of those of Cb, and Cc with all three kinds of term
-          const T dx_ruy = T(4) * vc.d_ruy + (vm.d_ruy + vn.d_ruy);
-          const T dx_muy = T(4) * vc.d_muy + (vm.d_muy + vn.d_muy);
-          const T dy_rux = vn.s_rux - vm.s_rux;
-          const T dy_mux = vn.s_mux - vm.s_mux;
-          Ca = T(-2) * ph.k12 * (dx_rux + dy_ruy) + (kr * T(1.0 / 6.0)) * (dx_ux + dy_uy) +
-               (T(1.0 / 3.0) - X * T(1.0 / 6.0)) * (dx_mux + dy_muy);
-          Cb = T(-2.0 / 3.0) * ph.k12 * (dx_rux - dy_ruy) + (kr * T(1.0 / 18.0)) * (dx_ux - dy_uy) +
-               T(1.0 / 18.0) * (dx_mux - dy_muy);
-          Cc = T(-1.0 / 3.0) * ph.k12 * (dx_ruy + dy_rux) + (kr * T(1.0 / 36.0)) * (dx_uy + dy_ux) +
-               T(1.0 / 36.0) * (dx_muy + dy_mux);
-        } else {
-          Ca = -ph.k12 * (dx_rux + dy_ruy) + (kr * T(1.0 / 6.0)) * (dx_ux + dy_uy) +
-               (T(0.25) - X * T(1.0 / 6.0)) * (dx_mux + dy_muy);
-          Cb = -ph.k12 * (dx_rux - dy_ruy) + (kr * T(1.0 / 18.0)) * (dx_ux - dy_uy) +
-               T(1.0 / 12.0) * (dx_mux - dy_muy);
-          Cc = (kr * T(1.0 / 36.0)) * (dx_uy + dy_ux);
-        }
-        if (DYN) Ca -= T(2) * X * rho * rC.dphi;  // moving phi (Eq. 20)
-        if constexpr (MASK) {
-          const unsigned nbC = (fl.hi >> 20) & 0x3FFu;
-          if (wave_any((nbC & BOUNCE) != 0)) {
-            // Solid neighbours stand in with the centre's velocity-like
-            // fields negated: each derivative gains -Kx (or -Ky) times the
-            // centre's rho u, u or (phi rho) u, here gathered into the three
-            // sums (rho u = rho (u), (phi rho) u = m0 (u))
-            const T kx = T(solid_kx(nbC)), ky = T(solid_ky(nbC));
-            const T sp = kx * ux + ky * uy, sm = kx * ux - ky * uy, sc = kx * uy + ky * ux;
-            if constexpr (EQ2) {  // the same with the coefficients of Eq. (B3)
-              Ca -= sp * ((kr * T(1.0 / 6.0) - T(2) * ph.k12 * rho) + (T(1.0 / 3.0) - X * T(1.0 / 6.0)) * m0);
-              Cb -= sm * ((kr * T(1.0 / 18.0) - T(2.0 / 3.0) * ph.k12 * rho) + T(1.0 / 18.0) * m0);
-              Cc -= sc * ((kr * T(1.0 / 36.0) - T(1.0 / 3.0) * ph.k12 * rho) + T(1.0 / 36.0) * m0);
-            } else {
-              Ca -= sp * ((kr * T(1.0 / 6.0) - ph.k12 * rho) + (T(0.25) - X * T(1.0 / 6.0)) * m0);
-              Cb -= sm * ((kr * T(1.0 / 18.0) - ph.k12 * rho) + T(1.0 / 12.0) * m0);
-              Cc -= sc * (kr * T(1.0 / 36.0));
-            }
-          }
-        }
-
-        // equilibria (Eq. 18) minus those of the rest state
-        const T drho = rC.drho;
-        const T uu = ux * ux + uy * uy;
-        const T eq_e = (ph.k2 - T(4) * phi) * drho + T(3) * m0 * uu;
-        const T eq_ep = (T(4) * phi - ph.k3) * drho - T(3) * m0 * uu;
-        const T qfac = EQ2 ? -m0 : (kappa - T(2) * phi) * rho;  // phi rho (X - 2), or -phi rho (B2)
-        const T eq_qx = qfac * ux, eq_qy = qfac * uy;
-        const T eq_pxx = m0 * (ux * ux - uy * uy);
-        const T eq_pxy = m0 * (ux * uy);
-
-        // force moments (Eq. 19)
-        const T uF = ux * Fx + uy * Fy;
-        const T S1 = T(6) * uF;
-        const T S7 = T(2) * (ux * Fx - uy * Fy);
-        const T S8 = ux * Fy + uy * Fx;
-
-        // relaxation (Eq. 16); conserved moments: m0+ = m0, j+ = j + F
-        const T he = ph.he, hep = ph.hep, hq = ph.hq, hn = ph.hn;
-        const T pe = rC.me - ph.s_e * (rC.me - eq_e) + he * (S1 + Ca);
-        const T pep = rC.mep - ph.s_eps * (rC.mep - eq_ep) - hep * S1;
-        const T pqx = rC.mqx - ph.s_q * (rC.mqx - eq_qx) - hq * Fx;
-        const T pqy = rC.mqy - ph.s_q * (rC.mqy - eq_qy) - hq * Fy;
-        const T ppxx = rC.mpxx - ph.s_nu * (rC.mpxx - eq_pxx) + hn * (S7 + Cb);
-        const T ppxy = rC.mpxy - ph.s_nu * (rC.mpxy - eq_pxy) + hn * (S8 + Cc);
-        const T pm0 = rC.dm0;
-        const T pjx = rC.jx + Fx;
-        const T pjy = rC.jy + Fy;
-
-        // back-transform f+ = M^-1 m+ (Eq. A1).  Half 1 with shifted storage
-        // takes the coefficients times the storage scale (a power of two, so
-        // the products are the scaled values exactly, as a multiply at the
-        // store would give them).
-        const bool scaled = SHIFT && half != 0;
-        const T c36 = scaled ? ph.bt36 : T(1.0 / 36.0), c6 = scaled ? ph.bt6 : T(1.0 / 6.0);
-        const T c12 = scaled ? ph.bt12 : T(1.0 / 12.0), c4 = scaled ? ph.bt4 : T(0.25);
-        const T c9 = scaled ? ph.bt9 : T(1.0 / 9.0);
-        const T a = (T(4) * pm0 - pe - T(2) * pep) * c36;
-        const T b = (T(4) * pm0 + T(2) * pe + pep) * c36;
-        const T X1 = (pjx - pqx) * c6, Y1 = (pjy - pqy) * c6;
-        const T X2 = (T(2) * pjx + pqx) * c12, Y2 = (T(2) * pjy + pqy) * c12;
-        const T Pd = ppxx * c4, Qd = ppxy * c4;
+        Derivs<T> d;
+        derivs2_of<FEAT>(vm, vc, vn, d);
         T o9[9];
-        o9[0] = (pm0 - pe + pep) * c9;
-        // the rows of M^-1 by their shared pairs: six additions fewer than
-        // summing each row's terms in turn
-        const T aP = a + Pd, aM = a - Pd, bP = b + Qd, bM = b - Qd;
-        const T sXY = X2 + Y2, dXY = X2 - Y2;
-        o9[1] = aP + X1;
-        o9[2] = aM + Y1;
-        o9[3] = aP - X1;
-        o9[4] = aM - Y1;
-        o9[5] = bP + sXY;
-        o9[6] = bM - dXY;
-        o9[7] = bP - sXY;
-        o9[8] = bM + dXY;
+        collide2_of<FEAT>(d, rC, (fl.hi >> 20) & 0x3FFu, vc.ux, vc.uy, bOld[0], bOld[1], kappa_less_one,
+                          SHIFT && half != 0, ph, o9);
+        const T phi = rC.phi;
         if (MASK && solid_bit(fl.hi, 20)) {  // solid node: keep the rest state
 #pragma unroll
           for (int i = 0; i < 9; ++i) o9[i] = T(0);
@@ -981,7 +1017,7 @@ __device__ inline void step2_tile(
         // a moving phi: the ring and shifted storage hold deviations from the
         // rest state of the void fraction the next pull runs at, whose rest_0
         // is rho0 d_t phi higher (times the storage scale for half 1's stores)
-        if (DYN && (half == 0 || SHIFT)) o9[0] -= (scaled ? ph.scale : T(1)) * (rho0 * rC.dphi);
+        if (DYN && (half == 0 || SHIFT)) o9[0] -= ((SHIFT && half != 0) ? ph.scale : T(1)) * (rho0 * rC.dphi);
 
         if (half == 0) {  // into the ring for the second step
           const int jo = jr(yo);

@@ -20,7 +20,7 @@ void launch_step_nt(const StepGeom& g, const StepPhys<T>& ph, int blocks, hipStr
 
 // One small lattice, `steps` time steps per launch of the tile kernel: one
 // workgroup per tile of g (g.strips tiles a row, each tile_out() nodes a side)
-template <typename S, typename T, bool SHIFT, int FEAT>
+template <typename S, typename T, bool SHIFT, int FEAT, bool PAIRS>
 void launch_tile(const StepGeom& g, const StepPhys<T>& ph, int walls, int steps, int blocks, hipStream_t st);
 
 // One lattice, two time steps per launch: `blocks` workgroups of two halves

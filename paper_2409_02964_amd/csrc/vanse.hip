@@ -444,8 +444,171 @@ int fused_rows(const vanse_lattice* h) {
   return (int)r;
 }
 
+// The instance of the tile kernel for single steps, or -1: the plain step with
+// any of the force field, the drag, solid nodes and walls in x (those with an
+// absent flag plane, which reads as zero), or a void fraction that moves now.
+// (A moving phi that is held constant adds nothing to the step: its lattices
+// take the instance without it.)
+int tile_inst(const vanse_lattice* h) {
+  const int f = feat_of(h);
+  if ((f & FEAT_SCHEME) || h->nee_lo || h->nee_hi) return -1;
+  const int fd = (h->d.has_force_field ? FEAT_FORCE : 0) | (h->d.has_drag ? FEAT_DRAG : 0);
+  if (h->phin_set) return (f & FEAT_MASK) ? -1 : FEAT_MOVING;
+  if (f & FEAT_MASK) return fd ? (FEAT_MASK | FEAT_FORCE | FEAT_DRAG) : FEAT_MASK;
+  return fd;
+}
+
+// The same for pairs of steps, of the lattices that the two-step kernel takes
+int tile_pair_inst(const vanse_lattice* h) {
+  const int f = fused_inst(h);
+  if (f < 0 || (f & (FEAT_SCHEME | FEAT_EQ2))) return -1;
+  return h->phin2_set ? FEAT_MOVING : tile_inst(h);
+}
+
+long long tile_blocks(const vanse_lattice* h, int steps) {
+  const int ox = tile_out(TILE_X, steps), oy = tile_out(tile_y(arith_bytes(h)), steps);
+  return (long long)((h->d.nx + ox - 1) / ox) * ((h->d.ny + oy - 1) / oy);
+}
+
+// Steps per launch of the tile kernel for n single steps, or 0 for the row
+// sweep (which also serves a launch shape that the caller chose).  As many as
+// leave every CU at most one tile (one workgroup fills a CU's registers), up
+// to four: more steps share a launch, but their tiles output less and
+// recompute more.  Where two steps need more than one round of tiles, they
+// still win while the rounds are few -- the line lies where both sides
+// measured alike, from 512 x 512 and 1003 x 777 nodes (us per step, sweep
+// against tiles): FP32 10.8/9.6 at 576 tiles, 18.5/21.8 at 1656; FP64 16.7/14.3
+// at 888, 27.3/34.6 at 2576; walls in x with a force field or drag, whose sweep
+// runs three waves per SIMD and carries a moving phi's planes, FP16 29.4/24.5
+// at 1656.  A single step (also a hand-over of phi, which takes one per call)
+// of several rounds is no faster than the sweep in FP32, and up to two rounds
+// in FP64.
+int tile_steps(const vanse_lattice* h, int64_t n) {
+  if (!h->tiling_default || tile_inst(h) < 0) return 0;
+  const int cus = device_cus();
+  const bool f64 = h->d.precision == VANSE_F64;
+  if (n == 1 || h->phin_set) return tile_blocks(h, 1) <= (f64 ? 2 : 1) * cus ? 1 : 0;
+  for (int k = 4; k >= 2; --k)
+    if (tile_blocks(h, k) <= cus) return k;
+  const bool slow_sweep = feat_of(h) == (FEAT_MASK | FEAT_MOVING);
+  const int rounds = slow_sweep ? 7 : (f64 ? 4 : 3);
+  return tile_blocks(h, 2) <= (long long)rounds * cus ? 2 : 0;
+}
+
+// Steps per launch of the tile kernel for pairs of steps (4 or 2), or 0 for
+// the two-step sweep (which also serves rows per workgroup that the caller
+// chose): by the same rule.  The sweep's twelve rows of pipeline take 9-13 us
+// a step however small the lattice.
+int tile_pair_steps(const vanse_lattice* h) {
+  if (h->rows2 > 0 || tile_pair_inst(h) < 0) return 0;
+  const int cus = device_cus();
+  if (!h->phin2_set && tile_blocks(h, 4) <= cus) return 4;
+  const int half_rounds = (h->d.precision == VANSE_F64 || h->d.has_mask) ? 8 : 5;
+  return 2 * tile_blocks(h, 2) <= (long long)half_rounds * cus ? 2 : 0;
+}
+
+// n steps with the tile kernel, at most k per launch, in units of `unit` steps
+// (2: pairs).  The number of launches is n / unit modulo two, so that a call
+// leaves the state in the same one of the two population buffers as launches
+// of one unit would (a captured even number of them can be replayed).
+template <typename S, typename T, bool SHIFT>
+int run_tiles(vanse_lattice* h, int64_t n, int k, int unit, hipStream_t st) {
+  n /= unit;
+  k /= unit;
+  if (n <= 0) return VANSE_OK;
+  const StepPhys<T> ph = make_phys<T>(h);
+  StepGeom g{};
+  g.nbr = h->d.has_mask ? h->ws + h->L.nbr : nullptr;
+  g.plane = h->L.plane;
+  g.nx = h->d.nx;
+  g.ny = h->d.ny;
+  g.pitch = h->L.pitch;
+  g.phi = h->ws + h->L.phi;
+  g.fxf = h->d.has_force_field ? h->ws + h->L.fx : nullptr;
+  g.fyf = h->d.has_force_field ? h->ws + h->L.fy : nullptr;
+  g.beta = h->d.has_drag ? h->ws + h->L.beta : nullptr;
+  if (h->d.dynamic_phi) {
+    g.phin = h->ws + h->L.phin;
+    g.phin2 = h->ws + h->L.phin2;
+    g.beta2 = h->beta2_set ? h->ws + h->L.beta2 : g.beta;
+    g.fxf2 = h->f2_set ? h->ws + h->L.fx2 : g.fxf;
+    g.fyf2 = h->f2_set ? h->ws + h->L.fy2 : g.fyf;
+  }
+  const int walls = (h->d.bc_y == VANSE_WALL ? 1 : 0) | (h->d.bc_x == VANSE_WALL ? 2 : 0);
+  const int feat = unit == 2 ? tile_pair_inst(h) : tile_inst(h);
+  int64_t launches = (n + k - 1) / k;
+  if ((launches ^ n) & 1) launches += 1;
+  const int64_t base = n / launches, more = n % launches;
+  for (int64_t s = 0; s < launches; ++s) {
+    const int steps = unit * (int)(base + (s < more ? 1 : 0));
+    const int ox = tile_out(TILE_X, steps);
+    g.strips = (h->d.nx + ox - 1) / ox;
+    const int blocks = (int)tile_blocks(h, steps);
+    g.src = h->ws + h->L.pop[h->cur];
+    g.dst = h->ws + h->L.pop[h->cur ^ 1];
+    auto go = [&](auto feat_c) {
+      constexpr int F = decltype(feat_c)::value;
+      if (unit == 2) launch_tile<S, T, SHIFT, F, true>(g, ph, walls, steps, blocks, st);
+      else launch_tile<S, T, SHIFT, F, false>(g, ph, walls, steps, blocks, st);
+    };
+    switch (feat) {
+      case FEAT_FORCE: go(std::integral_constant<int, FEAT_FORCE>{}); break;
+      case FEAT_DRAG: go(std::integral_constant<int, FEAT_DRAG>{}); break;
+      case FEAT_FORCE | FEAT_DRAG: go(std::integral_constant<int, FEAT_FORCE | FEAT_DRAG>{}); break;
+      case FEAT_MASK: go(std::integral_constant<int, FEAT_MASK>{}); break;
+      case FEAT_MASK | FEAT_FORCE | FEAT_DRAG:
+        go(std::integral_constant<int, FEAT_MASK | FEAT_FORCE | FEAT_DRAG>{});
+        break;
+      case FEAT_MOVING: go(std::integral_constant<int, FEAT_MOVING>{}); break;
+      default: go(std::integral_constant<int, 0>{});
+    }
+    h->cur ^= 1;
+    h->t += steps;
+    if (s == 0) HIP_TRY(hipGetLastError());
+  }
+  return VANSE_OK;
+}
+
+// A pending void fraction has been stepped to (two with the two-step
+// hand-over): the last step's inputs become the current ones.
+void hand_over2(vanse_lattice* h) {
+  if (!h->phin2_set) return;
+  std::swap(h->L.phi, h->L.phin2);
+  if (h->beta2_set) std::swap(h->L.beta, h->L.beta2);
+  if (h->f2_set) {
+    std::swap(h->L.fx, h->L.fx2);
+    std::swap(h->L.fy, h->L.fy2);
+  }
+  h->phin2_set = h->beta2_set = h->f2_set = false;
+  h->version += 1;
+}
+void hand_over1(vanse_lattice* h) {
+  if (h->phin_set) {  // phi(t+1) becomes the current void fraction
+    std::swap(h->L.phi, h->L.phin);
+    h->phin_set = false;
+    h->version += 1;
+  }
+  if (h->phin2_set) {
+    // the first of two pending steps is done: phi(t+2) is pending as the
+    // next phi(t+1), with the second step's force field and drag
+    std::swap(h->L.phin, h->L.phin2);
+    if (h->beta2_set) std::swap(h->L.beta, h->L.beta2);
+    if (h->f2_set) {
+      std::swap(h->L.fx, h->L.fx2);
+      std::swap(h->L.fy, h->L.fy2);
+    }
+    h->phin2_set = h->beta2_set = h->f2_set = false;
+    h->phin_set = true;
+  }
+}
+
 template <typename S, typename T, bool SHIFT>
 int run_fused_pairs(vanse_lattice* h, int64_t pairs, hipStream_t st) {
+  if (const int k = tile_pair_steps(h)) {
+    if (int rc = run_tiles<S, T, SHIFT>(h, 2 * pairs, k, 2, st)) return rc;
+    hand_over2(h);
+    return VANSE_OK;
+  }
   const StepPhys<T> ph = make_phys<T>(h);
   const int feat = fused_inst(h);
   StepGeom g{};
@@ -516,103 +679,9 @@ int run_fused_pairs(vanse_lattice* h, int64_t pairs, hipStream_t st) {
     }
     h->cur ^= 1;
     h->t += 2;
-    if (h->phin2_set) {  // the second step's inputs become the current ones
-      std::swap(h->L.phi, h->L.phin2);
-      if (h->beta2_set) std::swap(h->L.beta, h->L.beta2);
-      if (h->f2_set) {
-        std::swap(h->L.fx, h->L.fx2);
-        std::swap(h->L.fy, h->L.fy2);
-      }
-      h->phin2_set = h->beta2_set = h->f2_set = false;
-      h->version += 1;
-    }
+    hand_over2(h);
     if (s == 0) HIP_TRY(hipGetLastError());
   }
-  return VANSE_OK;
-}
-
-// The instance of the tile kernel that steps a lattice, or -1: the plain step
-// with any of the force field, the drag, solid nodes and walls in x (those
-// with an absent flag plane, which reads as zero).
-int tile_inst(const vanse_lattice* h) {
-  const int f = feat_of(h);
-  if (h->d.dynamic_phi || (f & FEAT_SCHEME)) return -1;
-  if (f & FEAT_MASK) return (f & (FEAT_FORCE | FEAT_DRAG)) ? (FEAT_MASK | FEAT_FORCE | FEAT_DRAG) : FEAT_MASK;
-  return f;
-}
-
-long long tile_blocks(const vanse_lattice* h, int steps) {
-  const int ox = tile_out(TILE_X, steps), oy = tile_out(tile_y(arith_bytes(h)), steps);
-  return (long long)((h->d.nx + ox - 1) / ox) * ((h->d.ny + oy - 1) / oy);
-}
-
-// Steps per launch of the tile kernel, or 0 for the row sweep (which also
-// serves a launch shape that the caller chose).  As many as leave every CU at
-// most one tile (one workgroup fills a CU's registers), up to four: more
-// steps share a launch, but their tiles output less and recompute more.
-// Where two steps need more than one round of tiles, they still win while the
-// rounds are few -- the line lies where both sides measured alike, from 512 x
-// 512 and 1003 x 777 nodes (us per step, sweep against tiles): FP32 10.8/9.6 at
-// 576 tiles, 18.5/21.8 at 1656; FP64 16.7/14.3 at 888, 27.3/34.6 at 2576; walls
-// in x with a force field or drag, whose sweep runs three waves per SIMD and
-// carries a moving phi's planes, FP16 29.4/24.5 at 1656.
-int tile_steps(const vanse_lattice* h) {
-  if (!h->tiling_default || tile_inst(h) < 0) return 0;
-  const int cus = device_cus();
-  for (int k = 4; k >= 2; --k)
-    if (tile_blocks(h, k) <= cus) return k;
-  const bool slow_sweep = feat_of(h) == (FEAT_MASK | FEAT_MOVING);
-  const int rounds = slow_sweep ? 7 : (h->d.precision == VANSE_F64 ? 4 : 3);
-  return tile_blocks(h, 2) <= (long long)rounds * cus ? 2 : 0;
-}
-
-// n steps with the tile kernel, at most k per launch.  The number of launches
-// is n modulo two, so that a call leaves the state in the same one of the two
-// population buffers as n single steps would (a captured even number of steps
-// can be replayed).
-template <typename S, typename T, bool SHIFT>
-int run_tiles(vanse_lattice* h, int64_t n, int k, hipStream_t st) {
-  if (n <= 0) return VANSE_OK;
-  const StepPhys<T> ph = make_phys<T>(h);
-  StepGeom g{};
-  g.nbr = h->d.has_mask ? h->ws + h->L.nbr : nullptr;
-  g.plane = h->L.plane;
-  g.nx = h->d.nx;
-  g.ny = h->d.ny;
-  g.pitch = h->L.pitch;
-  g.phi = h->ws + h->L.phi;
-  g.fxf = h->d.has_force_field ? h->ws + h->L.fx : nullptr;
-  g.fyf = h->d.has_force_field ? h->ws + h->L.fy : nullptr;
-  g.beta = h->d.has_drag ? h->ws + h->L.beta : nullptr;
-  const int walls = (h->d.bc_y == VANSE_WALL ? 1 : 0) | (h->d.bc_x == VANSE_WALL ? 2 : 0);
-  const int feat = tile_inst(h);
-  int64_t launches = (n + k - 1) / k;
-  if ((launches ^ n) & 1) launches += 1;
-  const int64_t base = n / launches, more = n % launches;
-  for (int64_t s = 0; s < launches; ++s) {
-    const int steps = (int)(base + (s < more ? 1 : 0));
-    const int ox = tile_out(TILE_X, steps);
-    g.strips = (h->d.nx + ox - 1) / ox;
-    const int blocks = (int)tile_blocks(h, steps);
-    g.src = h->ws + h->L.pop[h->cur];
-    g.dst = h->ws + h->L.pop[h->cur ^ 1];
-    switch (feat) {
-      case FEAT_FORCE: launch_tile<S, T, SHIFT, FEAT_FORCE>(g, ph, walls, steps, blocks, st); break;
-      case FEAT_DRAG: launch_tile<S, T, SHIFT, FEAT_DRAG>(g, ph, walls, steps, blocks, st); break;
-      case FEAT_FORCE | FEAT_DRAG:
-        launch_tile<S, T, SHIFT, FEAT_FORCE | FEAT_DRAG>(g, ph, walls, steps, blocks, st);
-        break;
-      case FEAT_MASK: launch_tile<S, T, SHIFT, FEAT_MASK>(g, ph, walls, steps, blocks, st); break;
-      case FEAT_MASK | FEAT_FORCE | FEAT_DRAG:
-        launch_tile<S, T, SHIFT, FEAT_MASK | FEAT_FORCE | FEAT_DRAG>(g, ph, walls, steps, blocks, st);
-        break;
-      default: launch_tile<S, T, SHIFT, 0>(g, ph, walls, steps, blocks, st);
-    }
-    h->cur ^= 1;
-    h->t += steps;
-    if (s == 0) HIP_TRY(hipGetLastError());
-  }
-  HIP_TRY(hipGetLastError());
   return VANSE_OK;
 }
 
@@ -633,9 +702,14 @@ int run_steps(vanse_lattice* h, int64_t n, hipStream_t st) {
     // void fraction, and the second step's inputs follow it (below)
     h->phin_set = true;
   }
-  // (a single step of several rounds of tiles is no faster than the sweep)
-  if (const int k = tile_steps(h))
-    if (n > 1 || tile_blocks(h, 1) <= device_cus()) return run_tiles<S, T, SHIFT>(h, n, k, st);
+  if (const int k = tile_steps(h, n)) {
+    // (with a void fraction pending, the first step alone: the second, of a
+    // two-step hand-over stepped singly, has inputs of its own)
+    const int64_t first = h->phin_set ? std::min<int64_t>(n, 1) : n;
+    if (int rc = run_tiles<S, T, SHIFT>(h, first, k, 1, st)) return rc;
+    if (first > 0) hand_over1(h);
+    return first < n ? run_steps<S, T, SHIFT>(h, n - first, st) : VANSE_OK;
+  }
   const StepPhys<T> ph = make_phys<T>(h);
   StepGeom g{};
   g.nbr = h->d.has_mask ? h->ws + h->L.nbr : nullptr;
@@ -663,23 +737,7 @@ int run_steps(vanse_lattice* h, int64_t n, hipStream_t st) {
     if (rc != VANSE_OK) return rc;
     h->cur ^= 1;
     h->t += 1;
-    if (h->phin_set) {  // phi(t+1) becomes the current void fraction
-      std::swap(h->L.phi, h->L.phin);
-      h->phin_set = false;
-      h->version += 1;
-    }
-    if (h->phin2_set) {
-      // the first of two pending steps is done: phi(t+2) is pending as the
-      // next phi(t+1), with the second step's force field and drag
-      std::swap(h->L.phin, h->L.phin2);
-      if (h->beta2_set) std::swap(h->L.beta, h->L.beta2);
-      if (h->f2_set) {
-        std::swap(h->L.fx, h->L.fx2);
-        std::swap(h->L.fy, h->L.fy2);
-      }
-      h->phin2_set = h->beta2_set = h->f2_set = false;
-      h->phin_set = true;
-    }
+    hand_over1(h);
     if (s == 0) HIP_TRY(hipGetLastError());
   }
   HIP_TRY(hipGetLastError());
