@@ -77,7 +77,7 @@ ReadShape read_shape(int nx, int ny) {
 }
 
 struct Layout {
-  size_t pop[2], phi, phin, nbr, fx, fy, beta, uprev, partials, partials2, result, badcount,
+  size_t pop[2], phi, phin, nbr, fx, fy, beta, spare, uprev, partials, partials2, result, badcount,
       check, total;
   // a moving phi: phi(t+2) and the second step's force field and drag
   // coefficient of a two-step hand-over (vanse_set_void_fraction_next2)
@@ -132,6 +132,7 @@ int make_layout(const vanse_desc* d, Layout* L) {
   }
   L->beta = 0;
   if (d->has_drag) { L->beta = off; off = align256(off + plane * cb); }
+  L->spare = off; off = align256(off + plane * cb);  // the next void fraction, until it is checked
   L->uprev = off; off = align256(off + 2 * plane * cb);
   L->max_partials = read_shape(d->nx, d->ny).blocks;
   L->partials = off; off = align256(off + L->max_partials * NOBS * sizeof(double));
@@ -775,6 +776,49 @@ dim3 field_grid(const vanse_lattice* h) { return dim3((h->d.nx + 255) / 256, h->
 
 }  // namespace
 
+// Small records that the device hands to the host (the flag of an upload, the
+// observables): 64 slots of 64 bytes in one page of pinned host memory, which
+// the device writes directly -- no copy between the kernel and the
+// synchronization.  The page is taken at the first use and kept; a call leases
+// a slot and gives it back when it returns, so calls from several threads, on
+// several streams and devices, each have one of their own.
+namespace {
+
+constexpr int kHostSlots = 64, kHostSlotBytes = 64;
+std::mutex g_host_mu;
+char* g_host_page = nullptr;
+unsigned long long g_host_used = 0;
+
+struct HostRecord {
+  char* p = nullptr;
+  int slot = -1;
+  int get() {  // a zeroed record, or an error
+    {
+      std::lock_guard<std::mutex> lock(g_host_mu);
+      if (!g_host_page)
+        HIP_TRY(hipHostMalloc((void**)&g_host_page, kHostSlots * kHostSlotBytes, hipHostMallocPortable));
+      if (~g_host_used) {
+        slot = __builtin_ctzll(~g_host_used);
+        g_host_used |= 1ull << slot;
+        p = g_host_page + slot * kHostSlotBytes;
+      }
+    }
+    if (!p) HIP_TRY(hipHostMalloc((void**)&p, kHostSlotBytes, hipHostMallocPortable));  // all leased
+    memset(p, 0, kHostSlotBytes);
+    return VANSE_OK;
+  }
+  ~HostRecord() {
+    if (slot >= 0) {
+      std::lock_guard<std::mutex> lock(g_host_mu);
+      g_host_used &= ~(1ull << slot);
+    } else if (p) {
+      (void)hipHostFree(p);
+    }
+  }
+};
+
+}  // namespace
+
 // Scratch of vanse_observe_noalloc: the FP64 block partials of one read-out
 // (one record per 256-column block of a row, at most kScratchBlocks), the
 // chunk records of the first reduction level and the final record.  Each
@@ -934,37 +978,52 @@ int vanse_set_body_force(vanse_lattice* h, double gx, double gy, int scale_by_ph
   return VANSE_OK;
 }
 
-// Check a dense phi field (solid nodes excepted) and convert it into the
-// plane at workspace offset `off`; solid nodes get the placeholder phi = 1.
-static int upload_phi(vanse_lattice* h, const double* phi, size_t off, hipStream_t st) {
-  unsigned long long* bad = reinterpret_cast<unsigned long long*>(h->ws + h->L.badcount);
-  HIP_TRY(hipMemsetAsync(bad, 0, sizeof(*bad), st));
-  const long long n = (long long)h->d.nx * h->d.ny;
-  const uint16_t* nbr = h->mask_set ? (const uint16_t*)(h->ws + h->L.nbr) : nullptr;
-  hipLaunchKernelGGL(count_bad_phi, dim3(256), dim3(256), 0, st, phi, h->d.nx, n, nbr, h->L.pitch, bad);
-  HIP_TRY(hipGetLastError());
-  unsigned long long nbad = 0;
-  HIP_TRY(hipMemcpyAsync(&nbad, bad, sizeof(nbad), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
-  if (nbad) return fail(VANSE_ERR_INVALID_ARG, "%llu void-fraction values outside (0, 1]", nbad);
-  void* dst = h->ws + off;
-  const Geo G = make_geo(h);
-  if (h->d.precision == VANSE_F64) {
-    hipLaunchKernelGGL(convert_field<double>, field_grid(h), dim3(256), 0, st, phi, (double*)dst, h->d.nx, h->d.ny, h->L.pitch);
-    if (nbr) hipLaunchKernelGGL(phi_on_solids<double>, field_grid(h), dim3(256), 0, st, G, (double*)dst, nbr);
-  } else {
-    hipLaunchKernelGGL(convert_field<float>, field_grid(h), dim3(256), 0, st, phi, (float*)dst, h->d.nx, h->d.ny, h->L.pitch);
-    if (nbr) hipLaunchKernelGGL(phi_on_solids<float>, field_grid(h), dim3(256), 0, st, G, (float*)dst, nbr);
+// Upload n fields (see upload_fields).  With void fractions among them the
+// stream is synchronized, and values outside (0, 1] are an error.
+static int upload(vanse_lattice* h, const UploadJob* jobs, int n, hipStream_t st) {
+  UploadJobs J{};
+  bool check = false;
+  for (int k = 0; k < n; ++k) {
+    J.job[k] = jobs[k];
+    check = check || jobs[k].check;
   }
+  const uint16_t* nbr = h->mask_set ? (const uint16_t*)(h->ws + h->L.nbr) : nullptr;
+  HostRecord rec;
+  if (check)
+    if (int rc = rec.get()) return rc;
+  dim3 grid = field_grid(h);
+  grid.z = (unsigned)n;
+  if (h->d.precision == VANSE_F64)
+    hipLaunchKernelGGL(upload_fields<double>, grid, dim3(256), 0, st, J, h->d.nx, h->d.ny, h->L.pitch, nbr, (int*)rec.p);
+  else
+    hipLaunchKernelGGL(upload_fields<float>, grid, dim3(256), 0, st, J, h->d.nx, h->d.ny, h->L.pitch, nbr, (int*)rec.p);
   HIP_TRY(hipGetLastError());
-  return VANSE_OK;
+  if (!check) return VANSE_OK;
+  HIP_TRY(hipStreamSynchronize(st));
+  if (*(volatile int*)rec.p == 0) return VANSE_OK;
+  unsigned long long* bad = reinterpret_cast<unsigned long long*>(h->ws + h->L.badcount);
+  for (int k = 0; k < n; ++k) {  // how many, of the first field that has any
+    if (!jobs[k].check) continue;
+    HIP_TRY(hipMemsetAsync(bad, 0, sizeof(*bad), st));
+    hipLaunchKernelGGL(count_bad_phi, dim3(256), dim3(256), 0, st, jobs[k].in, h->d.nx,
+                       (long long)h->d.nx * h->d.ny, nbr, h->L.pitch, bad);
+    HIP_TRY(hipGetLastError());
+    unsigned long long nbad = 0;
+    HIP_TRY(hipMemcpyAsync(&nbad, bad, sizeof(nbad), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (nbad) return fail(VANSE_ERR_INVALID_ARG, "%llu void-fraction values outside (0, 1]", nbad);
+  }
+  return fail(VANSE_ERR_INVALID_ARG, "void-fraction values outside (0, 1]");
 }
 
 int vanse_set_void_fraction(vanse_lattice* h, const double* phi, void* stream) {
   if (int rc = check_handle(h)) return rc;
   if (!phi) return fail(VANSE_ERR_INVALID_ARG, "phi is NULL");
   if (h->phin_set || h->phin2_set) return fail(VANSE_ERR_STATE, "phi(t+1) is pending; step first");
-  if (int rc = upload_phi(h, phi, h->L.phi, static_cast<hipStream_t>(stream))) return rc;
+  // into the spare plane: a field that is refused leaves the current one
+  const UploadJob job = {phi, h->ws + h->L.spare, 1};
+  if (int rc = upload(h, &job, 1, static_cast<hipStream_t>(stream))) return rc;
+  std::swap(h->L.phi, h->L.spare);
   h->phi_set = true;
   h->version += 1;
   return VANSE_OK;
@@ -976,7 +1035,8 @@ int vanse_set_void_fraction_next(vanse_lattice* h, const double* phi_next, void*
   if (!phi_next) return fail(VANSE_ERR_INVALID_ARG, "phi_next is NULL");
   if (!h->phi_set) return fail(VANSE_ERR_STATE, "void fraction not set");
   if (h->phin2_set) return fail(VANSE_ERR_STATE, "phi(t+1) and phi(t+2) are pending; step first");
-  if (int rc = upload_phi(h, phi_next, h->L.phin, static_cast<hipStream_t>(stream))) return rc;
+  const UploadJob job = {phi_next, h->ws + h->L.phin, 1};
+  if (int rc = upload(h, &job, 1, static_cast<hipStream_t>(stream))) return rc;
   h->phin_set = true;
   h->version += 1;
   return VANSE_OK;
@@ -994,20 +1054,14 @@ int vanse_set_void_fraction_next2(vanse_lattice* h, const double* phi_next, cons
   if ((fx_next != nullptr) != (fy_next != nullptr))
     return fail(VANSE_ERR_INVALID_ARG, "give both force planes of the second step, or neither");
   if (fx_next && !h->d.has_force_field) return fail(VANSE_ERR_STATE, "lattice was created without a force field");
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  if (int rc = upload_phi(h, phi_next, h->L.phin, st)) return rc;
-  if (int rc = upload_phi(h, phi_next2, h->L.phin2, st)) return rc;
-  const double* in[3] = {beta_next, fx_next, fy_next};
-  const size_t off[3] = {h->L.beta2, h->L.fx2, h->L.fy2};
-  for (int k = 0; k < 3; ++k) {
-    if (!in[k]) continue;
-    void* dst = h->ws + off[k];
-    if (h->d.precision == VANSE_F64)
-      hipLaunchKernelGGL(convert_field<double>, field_grid(h), dim3(256), 0, st, in[k], (double*)dst, h->d.nx, h->d.ny, h->L.pitch);
-    else
-      hipLaunchKernelGGL(convert_field<float>, field_grid(h), dim3(256), 0, st, in[k], (float*)dst, h->d.nx, h->d.ny, h->L.pitch);
+  UploadJob jobs[5] = {{phi_next, h->ws + h->L.phin, 1}, {phi_next2, h->ws + h->L.phin2, 1}};
+  int n = 2;
+  if (beta_next) jobs[n++] = {beta_next, h->ws + h->L.beta2, 0};
+  if (fx_next) {
+    jobs[n++] = {fx_next, h->ws + h->L.fx2, 0};
+    jobs[n++] = {fy_next, h->ws + h->L.fy2, 0};
   }
-  HIP_TRY(hipGetLastError());
+  if (int rc = upload(h, jobs, n, static_cast<hipStream_t>(stream))) return rc;
   h->phin2_set = true;
   h->beta2_set = beta_next != nullptr;
   h->f2_set = fx_next != nullptr;
@@ -1047,17 +1101,8 @@ int vanse_set_force_field(vanse_lattice* h, const double* fx, const double* fy, 
   if (int rc = check_handle(h)) return rc;
   if (!h->d.has_force_field) return fail(VANSE_ERR_STATE, "lattice was created without a force field");
   if (!fx || !fy) return fail(VANSE_ERR_INVALID_ARG, "force planes are NULL");
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  const double* in[2] = {fx, fy};
-  const size_t off[2] = {h->L.fx, h->L.fy};
-  for (int k = 0; k < 2; ++k) {
-    void* dst = h->ws + off[k];
-    if (h->d.precision == VANSE_F64)
-      hipLaunchKernelGGL(convert_field<double>, field_grid(h), dim3(256), 0, st, in[k], (double*)dst, h->d.nx, h->d.ny, h->L.pitch);
-    else
-      hipLaunchKernelGGL(convert_field<float>, field_grid(h), dim3(256), 0, st, in[k], (float*)dst, h->d.nx, h->d.ny, h->L.pitch);
-  }
-  HIP_TRY(hipGetLastError());
+  const UploadJob jobs[2] = {{fx, h->ws + h->L.fx, 0}, {fy, h->ws + h->L.fy, 0}};
+  if (int rc = upload(h, jobs, 2, static_cast<hipStream_t>(stream))) return rc;
   h->ff_set = true;
   return VANSE_OK;
 }
@@ -1067,13 +1112,8 @@ int vanse_set_drag(vanse_lattice* h, const double* beta, double usx, double usy,
   if (!h->d.has_drag) return fail(VANSE_ERR_STATE, "lattice was created without drag");
   if (!beta) return fail(VANSE_ERR_INVALID_ARG, "beta is NULL");
   if (!std::isfinite(usx) || !std::isfinite(usy)) return fail(VANSE_ERR_INVALID_ARG, "u_s must be finite");
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  void* dst = h->ws + h->L.beta;
-  if (h->d.precision == VANSE_F64)
-    hipLaunchKernelGGL(convert_field<double>, field_grid(h), dim3(256), 0, st, beta, (double*)dst, h->d.nx, h->d.ny, h->L.pitch);
-  else
-    hipLaunchKernelGGL(convert_field<float>, field_grid(h), dim3(256), 0, st, beta, (float*)dst, h->d.nx, h->d.ny, h->L.pitch);
-  HIP_TRY(hipGetLastError());
+  const UploadJob job = {beta, h->ws + h->L.beta, 0};
+  if (int rc = upload(h, &job, 1, static_cast<hipStream_t>(stream))) return rc;
   h->usx = usx;
   h->usy = usy;
   h->drag_set = true;
@@ -1275,13 +1315,20 @@ static int reduce_on_device(vanse_lattice* h, hipStream_t st) {
                        (double*)(h->ws + h->L.result), st);
 }
 
-// The same, copied to the host (synchronizes the stream).
-static int reduce_to_host(vanse_lattice* h, double* rec, hipStream_t st) {
-  if (int rc = reduce_on_device(h, st)) return rc;
-  const double* res = (const double*)(h->ws + h->L.result);
-  HIP_TRY(hipMemcpyAsync(rec, res, NOBS * sizeof(double), hipMemcpyDeviceToHost, st));
+// Reduce n partials to one record that the device writes into host memory
+// (synchronizes the stream).
+static int reduce_to_host(const double* in, long long n, double* mid, double* out, hipStream_t st) {
+  HostRecord rec;
+  if (int rc = rec.get()) return rc;
+  if (int rc = reduce_blocks(in, n, mid, (double*)rec.p, st)) return rc;
   HIP_TRY(hipStreamSynchronize(st));
+  for (int q = 0; q < NOBS; ++q) out[q] = ((volatile double*)rec.p)[q];
   return VANSE_OK;
+}
+
+static int reduce_to_host(vanse_lattice* h, double* out, hipStream_t st) {
+  return reduce_to_host((const double*)(h->ws + h->L.partials), read_shape(h->d.nx, h->d.ny).blocks,
+                        (double*)(h->ws + h->L.partials2), out, st);
 }
 
 int vanse_observe(vanse_lattice* h, double* out, void* stream) {
@@ -1309,13 +1356,10 @@ int vanse_observe_noalloc(vanse_lattice* h, double* out, void* stream) {
   if (int rc = scratch_of_device(&sp)) return rc;
   double* part = sp;
   double* mid = sp + kScratchBlocks * NOBS;
-  double* res = mid + 1024 * NOBS;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (int rc = moments_into(h, nullptr, nullptr, nullptr, nullptr, part, st, false)) return rc;
-  if (int rc = reduce_blocks(part, read_shape(h->d.nx, h->d.ny).blocks, mid, res, st)) return rc;
   double rec[NOBS];
-  HIP_TRY(hipMemcpyAsync(rec, res, NOBS * sizeof(double), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  if (int rc = reduce_to_host(part, read_shape(h->d.nx, h->d.ny).blocks, mid, rec, st)) return rc;
   for (int q = 0; q < 4; ++q) out[q] = rec[q];
   if (out[3] > 0) return fail(VANSE_ERR_DIVERGED, "%.0f nodes hold non-finite values at t = %lld", out[3], (long long)h->t);
   return VANSE_OK;
