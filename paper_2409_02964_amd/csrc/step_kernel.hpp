@@ -248,19 +248,20 @@ __device__ __forceinline__ void deviations(const V (&f)[9], T phi, const StepPhy
 
 // Stored values of post-collision deviations o on a node whose next pull runs
 // at the void fraction phi (+ dphi when it moves: rest_0 changes by rho0
-// d_t phi, which shifted storage takes out here)
-template <typename S, typename T, bool SHIFT, int FEAT>
-__device__ __forceinline__ void stored(T (&o)[9], T phi, T dphi, const StepPhys<T>& ph, S (&v)[9]) {
+// d_t phi, which shifted storage takes out here), each handed to put(i, value)
+// as it is formed
+template <typename S, typename T, bool SHIFT, int FEAT, typename F>
+__device__ __forceinline__ void stored(T (&o)[9], T phi, T dphi, const StepPhys<T>& ph, F&& put) {
   if (SHIFT && (FEAT & FEAT_DYNPHI)) o[0] -= ph.rho0 * dphi;
   if (SHIFT) {
 #pragma unroll
-    for (int i = 0; i < 9; ++i) v[i] = static_cast<S>(sizeof(S) == 2 ? o[i] * ph.scale : o[i]);
+    for (int i = 0; i < 9; ++i) put(i, static_cast<S>(sizeof(S) == 2 ? o[i] * ph.scale : o[i]));
   } else {
-    v[0] = static_cast<S>(o[0] + (phi * ph.rho0 - ph.rest0_k));
+    put(0, static_cast<S>(o[0] + (phi * ph.rho0 - ph.rest0_k)));
 #pragma unroll
-    for (int i = 1; i < 5; ++i) v[i] = static_cast<S>(o[i] + ph.rest_axis);
+    for (int i = 1; i < 5; ++i) put(i, static_cast<S>(o[i] + ph.rest_axis));
 #pragma unroll
-    for (int i = 5; i < 9; ++i) v[i] = static_cast<S>(o[i] + ph.rest_diag);
+    for (int i = 5; i < 9; ++i) put(i, static_cast<S>(o[i] + ph.rest_diag));
   }
 }
 
@@ -768,10 +769,7 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
       derivs_of<FEAT>(v, rC, ph, [&](int i) { return s_u2[uo][i == 0 ? tc : (i == 1 ? tr : tl)]; }, d);
       collide_of<FEAT>(d, rC, v.C.ux, v.C.uy, bOld[0], bOld[1], ph, o9);
       auto store_row = [&](T (&o)[9], T ph_n, T dph_n, int r) {
-        S sv[9];
-        stored<S, T, SHIFT, FEAT>(o, ph_n, dph_n, ph, sv);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) bstore(sv[i], dstr, xcb, poff(i, r));
+        stored<S, T, SHIFT, FEAT>(o, ph_n, dph_n, ph, [&](int i, S v) { bstore(v, dstr, xcb, poff(i, r)); });
       };
 
       if constexpr (NEE) {

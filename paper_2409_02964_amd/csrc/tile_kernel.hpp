@@ -274,7 +274,7 @@ vanse_tile_kernel(StepGeom g, StepPhys<T> ph, int walls, int steps) {
 #pragma unroll
           for (int i = 0; i < 9; ++i) out[i] = static_cast<S>(o9[i]);
         } else if (second) {
-          stored<S, T, false, 0>(o9, r.phi, T(0), ph, out);
+          stored<S, T, false, 0>(o9, r.phi, T(0), ph, [&](int i, S x) { out[i] = x; });
         }
       } else {
         // a solid neighbour stands in with the centre's, negated
@@ -315,7 +315,7 @@ vanse_tile_kernel(StepGeom g, StepPhys<T> ph, int walls, int steps) {
         }
         __builtin_amdgcn_sched_barrier(0);
         collide_of<FEAT>(d, r, uc.a, uc.b, Fx, Fy, ph, o9);
-        stored<S, T, SHIFT, FEAT>(o9, phi, r.dphi, ph, out);
+        stored<S, T, SHIFT, FEAT>(o9, phi, r.dphi, ph, [&](int i, S x) { out[i] = x; });
       }
     }
     if (step == steps) {
