@@ -375,11 +375,18 @@ __device__ __forceinline__ void velocity2_of(T grx, T gry, const RowState<T>& r,
   b.muy = m0 * uy; b.ruy = rho * uy;
 }
 
-// 12 times the derivatives at a node (Derivs) from the separable sums of the
+// 12 times the derivatives of the penalty source at a node, with the four
+// more of Appendix B's (FEAT_EQ2)
+template <typename T>
+struct Derivs2 : Derivs<T> {
+  T ruy_x, muy_x, rux_y, mux_y;
+};
+
+// The derivatives from the separable sums of the
 // rows below (m), of the node (c) and above (n)
 template <int FEAT, typename T>
 __device__ __forceinline__ void derivs2_of(const VelDS<T>& vm, const VelDS<T>& vc, const VelDS<T>& vn,
-                                           Derivs<T>& d) {
+                                           Derivs2<T>& d) {
   d.rux_x = T(4) * vc.d_rux + (vm.d_rux + vn.d_rux);
   d.ux_x = T(4) * vc.d_ux + (vm.d_ux + vn.d_ux);
   d.uy_x = T(4) * vc.d_uy + (vm.d_uy + vn.d_uy);
@@ -400,7 +407,7 @@ __device__ __forceinline__ void derivs2_of(const VelDS<T>& vm, const VelDS<T>& v
 // penalty source, collision and back-transform into the deviations o9, times
 // the storage scale with `scaled`.  nbC: solid flags.
 template <int FEAT, typename T>
-__device__ __forceinline__ void collide2_of(const Derivs<T>& d, const RowState<T>& rC, unsigned nbC, T ux, T uy,
+__device__ __forceinline__ void collide2_of(const Derivs2<T>& d, const RowState<T>& rC, unsigned nbC, T ux, T uy,
                                             T Fx, T Fy, bool kappa_less_one, bool scaled,
                                             const StepPhys<T>& ph, T (&o9)[9]) {
   constexpr bool MASK = (FEAT & FEAT_MASK) != 0, DYN = (FEAT & FEAT_DYNPHI) != 0, EQ2 = (FEAT & FEAT_EQ2) != 0;
@@ -1004,7 +1011,7 @@ __device__ inline void step2_tile(
         }
       }
       if (rowC && olane) {
-        Derivs<T> d;
+        Derivs2<T> d;
         derivs2_of<FEAT>(vm, vc, vn, d);
         T o9[9];
         collide2_of<FEAT>(d, rC, (fl.hi >> 20) & 0x3FFu, vc.ux, vc.uy, bOld[0], bOld[1], kappa_less_one,

@@ -35,6 +35,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace vanse_dev {
 
 // Per-node velocity data shared with the neighbours through LDS: u, the
@@ -131,9 +133,6 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
   const int x = b & 7, i = b >> 3, q = nb >> 3, r = nb & 7;
   return x * q + min(x, r) + i;
 }
-
-// LDS ring slot of a (possibly negative) row index: four rows per ring
-__device__ __forceinline__ int slot4(int y) { return y & 3; }
 
 // Reciprocal: the hardware v_rcp_f32 (1 ulp) in FP32, a correctly rounded
 // division in FP64.
@@ -288,11 +287,18 @@ struct RhoAround {
 };
 
 // Stage B of a node: F (Eq. 13 and F^B), u (Eq. 7) and the products that the
-// penalty derivatives act on; solid neighbours take the centre's delta-rho
-template <int FEAT, typename T>
-__device__ __forceinline__ void velocity_of(RhoAround<T> n, const RowState<T>& r, T ffx, T ffy,
+// penalty derivatives act on; solid neighbours take the centre's delta-rho.
+// force(x, y) gives the force field of the node: asked for first, so that its
+// loads land meanwhile (95 -> 90 us per step on 2900 x 1500 FP32 with drag), but
+// where registers are short (FP32 with solid nodes or a scheme variant) only
+// when it is needed.
+template <int FEAT, typename T, typename FF>
+__device__ __forceinline__ void velocity_of(RhoAround<T> n, const RowState<T>& r, FF&& force,
                                             const StepPhys<T>& ph, U4<T>& a, U2<T>& b, T& Fx, T& Fy,
                                             T& m0, T& rho) {
+  constexpr bool EARLY = sizeof(T) == 8 || (FEAT & (FEAT_MASK | FEAT_SCHEME)) == 0;
+  T ffx = T(0), ffy = T(0);
+  if ((FEAT & FEAT_FORCE) && EARLY) force(ffx, ffy);
   if constexpr ((FEAT & FEAT_MASK) != 0) {
     const unsigned nb = r.nb;
     const T rc = r.drho;
@@ -314,6 +320,7 @@ __device__ __forceinline__ void velocity_of(RhoAround<T> n, const RowState<T>& r
   Fx = kp * grx + sg * ph.gx;
   Fy = kp * gry + sg * ph.gy;
   if (FEAT & FEAT_FORCE) {
+    if (!EARLY) force(ffx, ffy);
     Fx += ffx;
     Fy += ffy;
   }
@@ -344,19 +351,28 @@ struct VelAround {
   U2<T> bN, bS, bNE, bNW, bSE, bSW;
 };
 
-// The derivatives of the penalty source, and four more for Appendix B's
+// The eight derivatives of the penalty source of Eq. (20) at a node
 template <typename T>
 struct Derivs {
-  T rux_x, ruy_y, ux_x, uy_y, uy_x, ux_y, mux_x, muy_y;  // Eq. (20)
-  T ruy_x, muy_x, rux_y, mux_y;                          // Eq. (B3)
+  T rux_x, ruy_y, ux_x, uy_y, uy_x, ux_y, mux_x, muy_y;
 };
 
-// The derivatives at a node by Eq. (10).  u2 gives the U2 record of the
-// centre (0), the east (1) and the west (3) node, for solid neighbours and
-// the Appendix B penalty.
+// Eq. (20) from its derivatives by Eq. (10), but for the d_t phi term
+template <typename T>
+__device__ __forceinline__ void penalty20(const Derivs<T>& d, T kappa, T kmp, T rho, T X, T& Ca, T& Cb, T& Cc) {
+  Ca = -kappa * (d.rux_x + d.ruy_y) + T(2) * kmp * rho * (d.ux_x + d.uy_y) +
+       (T(3) - T(2) * X) * (d.mux_x + d.muy_y);
+  Cb = -kappa * (d.rux_x - d.ruy_y) + T(2.0 / 3.0) * kmp * rho * (d.ux_x - d.uy_y) +
+       (d.mux_x - d.muy_y);
+  Cc = T(1.0 / 3.0) * kmp * rho * (d.uy_x + d.ux_y);
+}
+
+// The penalty source of a node: the eight derivatives of Eq. (20), or the
+// twelve of Eq. (B3) for the second-order equilibrium.  u2 gives the U2 record
+// of the centre (0), the east (1) and the west (3) node.
 template <int FEAT, typename T, typename F2>
-__device__ __forceinline__ void derivs_of(VelAround<T>& v, const RowState<T>& rC, const StepPhys<T>& ph,
-                                          F2&& u2, Derivs<T>& d) {
+__device__ __forceinline__ void penalty_of(VelAround<T>& v, const RowState<T>& rC, const StepPhys<T>& ph,
+                                           F2&& u2, T& Ca, T& Cb, T& Cc) {
   const U4<T> aC = v.C;
   if constexpr ((FEAT & FEAT_MASK) != 0) {
     // solid neighbour: the centre's velocity-like fields, negated
@@ -379,6 +395,7 @@ __device__ __forceinline__ void derivs_of(VelAround<T>& v, const RowState<T>& rC
     sel4(v.NE, 5); sel4(v.NW, 6); sel4(v.SW, 7); sel4(v.SE, 8);
     sel2(v.bN, 2); sel2(v.bS, 4); sel2(v.bNE, 5); sel2(v.bNW, 6); sel2(v.bSW, 7); sel2(v.bSE, 8);
   }
+  Derivs<T> d;
   // the eight derivatives of Eq. (20), each by Eq. (10)
   d.rux_x = stencil_dx(v.E.rux, v.W.rux, v.NE.rux, v.SE.rux, v.NW.rux, v.SW.rux);
   d.ruy_y = stencil_dy(v.bN.ruy, v.bS.ruy, v.bNE.ruy, v.bNW.ruy, v.bSE.ruy, v.bSW.ruy);
@@ -388,6 +405,12 @@ __device__ __forceinline__ void derivs_of(VelAround<T>& v, const RowState<T>& rC
   d.ux_y = stencil_dy(v.N.ux, v.S.ux, v.NE.ux, v.NW.ux, v.SE.ux, v.SW.ux);
   d.mux_x = stencil_dx(v.E.mux, v.W.mux, v.NE.mux, v.SE.mux, v.NW.mux, v.SW.mux);
   d.muy_y = stencil_dy(v.bN.muy, v.bS.muy, v.bNE.muy, v.bNW.muy, v.bSE.muy, v.bSW.muy);
+
+  const T phi = rC.phi;
+  const T rho = ph.rho0 + rC.drho, kappa = ph.kappa;
+  const T X = kappa * recip(phi);
+  const T kmp = kappa - (((FEAT & FEAT_SCHEME) && ph.model_b) ? T(1) : phi);
+  // d_t phi = phi(t+1) - phi(t), zero when static
   if ((FEAT & FEAT_SCHEME) && ph.eq2) {
     U2<T> bE = u2(1), bW = u2(3);
     if constexpr ((FEAT & FEAT_MASK) != 0) {
@@ -396,44 +419,30 @@ __device__ __forceinline__ void derivs_of(VelAround<T>& v, const RowState<T>& rC
       bE.muy = sE ? -bC.muy : bE.muy; bE.ruy = sE ? -bC.ruy : bE.ruy;
       bW.muy = sW ? -bC.muy : bW.muy; bW.ruy = sW ? -bC.ruy : bW.ruy;
     }
-    d.ruy_x = stencil_dx(bE.ruy, bW.ruy, v.bNE.ruy, v.bSE.ruy, v.bNW.ruy, v.bSW.ruy);
-    d.muy_x = stencil_dx(bE.muy, bW.muy, v.bNE.muy, v.bSE.muy, v.bNW.muy, v.bSW.muy);
-    d.rux_y = stencil_dy(v.N.rux, v.S.rux, v.NE.rux, v.NW.rux, v.SE.rux, v.SW.rux);
-    d.mux_y = stencil_dy(v.N.mux, v.S.mux, v.NE.mux, v.NW.mux, v.SE.mux, v.SW.mux);
-  }
-}
-
-// Stage C of a node from the derivatives d and the velocity (ux, uy): the
-// penalty source, collision (Eq. 16-19) and back-transform (Eq. A1) into the
-// deviations o9.
-template <int FEAT, typename T>
-__device__ __forceinline__ void collide_of(const Derivs<T>& d, const RowState<T>& rC, T ux, T uy, T Fx, T Fy,
-                                           const StepPhys<T>& ph, T (&o9)[9]) {
-  const T phi = rC.phi;
-  const T rho = ph.rho0 + rC.drho, kappa = ph.kappa;
-  const T X = kappa * recip(phi);
-  const bool eq2 = (FEAT & FEAT_SCHEME) && ph.eq2;
-  const T kmp = kappa - (((FEAT & FEAT_SCHEME) && ph.model_b) ? T(1) : phi);
-
-  // penalty source (Eq. 20, or B3 for the second-order equilibrium);
-  // d.t phi = phi(t+1) - phi(t), zero when static
-  T Ca, Cb, Cc;
-  if (eq2) {
+    const T d_ruy_x = stencil_dx(bE.ruy, bW.ruy, v.bNE.ruy, v.bSE.ruy, v.bNW.ruy, v.bSW.ruy);
+    const T d_muy_x = stencil_dx(bE.muy, bW.muy, v.bNE.muy, v.bSE.muy, v.bNW.muy, v.bSW.muy);
+    const T d_rux_y = stencil_dy(v.N.rux, v.S.rux, v.NE.rux, v.NW.rux, v.SE.rux, v.SW.rux);
+    const T d_mux_y = stencil_dy(v.N.mux, v.S.mux, v.NE.mux, v.NW.mux, v.SE.mux, v.SW.mux);
     Ca = T(-2) * kappa * (d.rux_x + d.ruy_y) + T(2) * kmp * rho * (d.ux_x + d.uy_y) +
          (T(4) - T(2) * X) * (d.mux_x + d.muy_y);
     Cb = T(-2.0 / 3.0) * kappa * (d.rux_x - d.ruy_y) +
          T(2.0 / 3.0) * kmp * rho * (d.ux_x - d.uy_y) + T(2.0 / 3.0) * (d.mux_x - d.muy_y);
-    Cc = -T(1.0 / 3.0) * kappa * (d.ruy_x + d.rux_y) + T(1.0 / 3.0) * kmp * rho * (d.uy_x + d.ux_y) +
-         T(1.0 / 3.0) * (d.muy_x + d.mux_y);
+    Cc = -T(1.0 / 3.0) * kappa * (d_ruy_x + d_rux_y) + T(1.0 / 3.0) * kmp * rho * (d.uy_x + d.ux_y) +
+         T(1.0 / 3.0) * (d_muy_x + d_mux_y);
   } else {
-    Ca = -kappa * (d.rux_x + d.ruy_y) + T(2) * kmp * rho * (d.ux_x + d.uy_y) +
-         (T(3) - T(2) * X) * (d.mux_x + d.muy_y);
-    Cb = -kappa * (d.rux_x - d.ruy_y) + T(2.0 / 3.0) * kmp * rho * (d.ux_x - d.uy_y) +
-         (d.mux_x - d.muy_y);
-    Cc = T(1.0 / 3.0) * kmp * rho * (d.uy_x + d.ux_y);
+    penalty20(d, kappa, kmp, rho, X, Ca, Cb, Cc);
   }
   if (FEAT & FEAT_DYNPHI) Ca -= T(2) * X * rho * rC.dphi;
+}
 
+// Stage C of a node from its penalty source and velocity: collision (Eq.
+// 16-19) and back-transform (Eq. A1) into the deviations o9
+template <int FEAT, typename T>
+__device__ __forceinline__ void collide_of(T Ca, T Cb, T Cc, const RowState<T>& rC, T ux, T uy, T Fx, T Fy,
+                                           const StepPhys<T>& ph, T (&o9)[9]) {
+  const T phi = rC.phi;
+  const T rho = ph.rho0 + rC.drho, kappa = ph.kappa;
+  const bool eq2 = (FEAT & FEAT_SCHEME) && ph.eq2;
   // equilibria (Eq. 18) minus those of the rest state
   const T m0 = phi * ph.rho0 + rC.dm0;  // phi rho
   const T drho = rC.drho;
@@ -494,20 +503,32 @@ __device__ __forceinline__ void collide_of(const Derivs<T>& d, const RowState<T>
 // FEAT: FEAT_FORCE adds the per-node force planes to F^B; FEAT_DRAG adds
 //       the linear drag -phi beta (u - u_s) with u solved in closed form
 // NT: threads per workgroup (= out_w + 4 active lanes at most)
-// LDS rings over the last four rows.  Next to a wall the row beyond it is
-// filled with the mirror image (scalars copied, velocities negated), so the
-// stencils never test for walls.
+// LDS rings over the last rows.  Next to a wall the row beyond it is filled
+// with the mirror image (scalars copied, velocities negated), so the stencils
+// never test for walls.
+// FP64: three rows, the row that a stage writes taking the slot of the row
+// three below it, which was last read a barrier ago.  The sweep is unrolled by
+// a multiple of three, so a row's slot is a constant of the code and, with an
+// element of room at either end, every LDS address an immediate offset from
+// one register per ring; slots by the row modulo four cost 33 of 285 vector
+// instructions a row in address arithmetic.  2 to 11% faster (us per step, 2048 x
+// 2048: plain 144 -> 143, drag and force field 167 -> 164, moving phi 167 -> 151,
+// model B 169 -> 155).  FP32: four rows, the slot the row modulo four, since
+// the three-row ring gained nothing there and cost the instances with solid
+// nodes 1-8%.
+template <typename T>
+constexpr bool ring3() { return sizeof(T) == 8; }
 template <typename T, int NT>
 struct StepLds {
-  T rho[4][NT];      // delta-rho (stage A -> stage B)
-  U4<T> u4[4][NT];   // (stage B -> stage C)
-  U2<T> u2[4][NT];
+  static constexpr int ROWS = ring3<T>() ? 3 : 4, LEN = NT + (ring3<T>() ? 2 : 0);
+  T rho[ROWS][LEN];      // delta-rho (stage A -> stage B)
+  U4<T> u4[ROWS][LEN];   // (stage B -> stage C)
+  U2<T> u2[ROWS][LEN];
 };
 
 // One workgroup's tile: strip `strip` (columns strip*out_w .. +out_w-1) and
 // row block `by` (rows by*rows .. +rows-1) of the lattice described by g.
-// PD: prefetch distance in rows (1 or 2).
-template <typename S, typename T, bool SHIFT, bool WALLS, int FEAT, int NT, int PD>
+template <typename S, typename T, bool SHIFT, bool WALLS, int FEAT, int NT>
 __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& ph, int strip,
                                           int by, StepLds<T, NT>& L) {
   auto& s_rho = L.rho;
@@ -544,7 +565,10 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
   // per-lane conditions (kept as lane masks, not registers)
   const bool xmir = xw && (xg < 0 || xg >= nx);
   const bool xlo = xw && c == 0, xhi = xw && c == nx - 1;
-  const int tl = max(tc - 1, 0), tr = min(tc + 1, NT - 1);
+  // positions in the rings of this lane and of lane tc and its neighbours
+  constexpr bool R3 = ring3<T>();
+  const int pt = R3 ? t + 1 : t, pc = R3 ? tc + 1 : tc;
+  const int pl = R3 ? tc : max(tc - 1, 0), pr = R3 ? tc + 2 : min(tc + 1, NT - 1);
   constexpr unsigned SB = sizeof(S);
   constexpr unsigned TB = sizeof(T);
   // velocity boundary rows: built into the instance with every feature only
@@ -636,10 +660,13 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
 
   // One sweep iteration.  A: row yn, B: row yn-1, C: row yn-2.  rA is
   // written, rB/rC are read; bNew is written by B, bOld (row yn-2) read by C.
-  auto body = [&](int k, const RowIn<S, T>& in, RowState<T>& rA,
+  auto body = [&](auto i6, int k, const RowIn<S, T>& in, RowState<T>& rA,
                   const RowState<T>& rB, const RowState<T>& rC, T (&bNew)[2],
                   const T (&bOld)[2]) {
+    constexpr int I = decltype(i6)::value;
     const int yn = y0 - 2 + k;
+    // ring slot of row y, the c-th of the unrolled sweep modulo three
+    auto slot = [](int y, int c) { return R3 ? c % 3 : y & 3; };
     const S (&f)[9] = in.f;
     // FP16 and FP64 storage: the waves in stages A and B (the short phase up
     // to the second barrier) issue before the waves in stage C (s_setprio;
@@ -679,37 +706,51 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
       rA.dphi = (FEAT & FEAT_DYNPHI) ? phin_in - phi : T(0);
       rA.nb = (FEAT & FEAT_MASK) ? nb_in : 0u;
       rA.drho = rA.dm0 * recip(phi);
-      s_rho[slot4(yn)][t] = rA.drho;
-      if (WALLS && yn == 0) s_rho[slot4(-1)][t] = rA.drho;      // image below
-      if (WALLS && yn == ny - 1) s_rho[slot4(ny)][t] = rA.drho; // image above
+      s_rho[slot(yn, I)][pt] = rA.drho;
+      if (WALLS && yn == 0) s_rho[slot(-1, I + 2)][pt] = rA.drho;  // image below
+      if (WALLS && !R3 && yn == ny - 1) s_rho[slot(ny, 0)][pt] = rA.drho;  // image above
       if constexpr (NEE) {
         // a velocity row takes the density of the fluid row next to it
-        if (ph.nee_lo && yn == 1) s_rho[slot4(0)][t] = rA.drho;
-        if (ph.nee_hi && yn == ny - 1) s_rho[slot4(yn)][t] = rB.drho;
+        if (ph.nee_lo && yn == 1) s_rho[slot(0, I + 2)][pt] = rA.drho;
+        if (ph.nee_hi && yn == ny - 1) s_rho[slot(yn, I)][pt] = rB.drho;
       }
+    } else if (WALLS && R3 && yn == ny) {
+      s_rho[slot(yn, I)][pt] = rB.drho;  // image above, once its slot is free
     }
     __syncthreads();
 
     // ---------------- stage B: velocity of row yn-1 ----------------
     const int yb = yn - 1;
+    // the image of a row beyond a wall of velocity uw, into slot sl
+    auto image = [&](const U4<T>& a, const U2<T>& b, T m0, T rho, T uw, int sl) {
+      U4<T> am;
+      U2<T> bm;
+      am.ux = -a.ux; am.uy = -a.uy; am.mux = -a.mux; am.rux = -a.rux;
+      if constexpr ((FEAT & FEAT_SCHEME) != 0) {  // moving wall: u -> 2 u_w - u
+        const T uw2 = T(2) * uw;
+        am.ux += uw2; am.mux += uw2 * m0; am.rux += uw2 * rho;
+      }
+      bm.muy = -b.muy; bm.ruy = -b.ruy;
+      s_u4[sl][pt] = am;
+      s_u2[sl][pt] = bm;
+    };
     const bool rowB = (yb >= y0 - 1) && (WALLS ? (yb >= 0 && yb < ny) : true);
     if (rowB && ulane) {
-      const int sc = slot4(yb), ss = slot4(yb - 1), sn = slot4(yb + 1);
+      const int sc = slot(yb, I + 2), ss = slot(yb - 1, I + 1), sn = slot(yb + 1, I);
       RhoAround<T> n;
-      n.E = s_rho[sc][tr]; n.W = s_rho[sc][tl];
-      n.N = s_rho[sn][tc]; n.S = s_rho[ss][tc];
-      n.NE = s_rho[sn][tr]; n.NW = s_rho[sn][tl];
-      n.SE = s_rho[ss][tr]; n.SW = s_rho[ss][tl];
-      T ffx = T(0), ffy = T(0);
-      if (FEAT & FEAT_FORCE) {
+      n.E = s_rho[sc][pr]; n.W = s_rho[sc][pl];
+      n.N = s_rho[sn][pc]; n.S = s_rho[ss][pc];
+      n.NE = s_rho[sn][pr]; n.NW = s_rho[sn][pl];
+      n.SE = s_rho[ss][pr]; n.SW = s_rho[ss][pl];
+      auto force = [&](T& x, T& y) {
         const unsigned ro = unsigned(WALLS ? yb : wrap_index(yb, ny)) * unsigned(pitch) * TB;
-        ffx = bload<T>(fxr, xcT, ro);
-        ffy = bload<T>(fyr, xcT, ro);
-      }
+        x = bload<T>(fxr, xcT, ro);
+        y = bload<T>(fyr, xcT, ro);
+      };
       U4<T> a;
       U2<T> b;
       T m0, rho;
-      velocity_of<FEAT>(n, rB, ffx, ffy, ph, a, b, bNew[0], bNew[1], m0, rho);
+      velocity_of<FEAT>(n, rB, force, ph, a, b, bNew[0], bNew[1], m0, rho);
       if constexpr (NEE) {
         // velocity row: the wall velocity, with the density of the fluid row
         // next to it (row 1 is this iteration's stage-A row, row ny - 2 its
@@ -728,25 +769,24 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
         ax.ux = xmir ? -a.ux : a.ux; ax.uy = xmir ? -a.uy : a.uy;
         ax.mux = xmir ? -a.mux : a.mux; ax.rux = xmir ? -a.rux : a.rux;
         bx.muy = xmir ? -b.muy : b.muy; bx.ruy = xmir ? -b.ruy : b.ruy;
-        s_u4[slot4(yb)][t] = ax;
-        s_u2[slot4(yb)][t] = bx;
+        s_u4[slot(yb, I + 2)][pt] = ax;
+        s_u2[slot(yb, I + 2)][pt] = bx;
       } else {
-        s_u4[slot4(yb)][t] = a;
-        s_u2[slot4(yb)][t] = b;
+        s_u4[slot(yb, I + 2)][pt] = a;
+        s_u2[slot(yb, I + 2)][pt] = b;
       }
-      if (WALLS && (yb == 0 || yb == ny - 1)) {  // mirror image beyond the wall
-        const int sg2 = slot4(yb == 0 ? -1 : ny);
-        U4<T> am;
-        U2<T> bm;
-        am.ux = -a.ux; am.uy = -a.uy; am.mux = -a.mux; am.rux = -a.rux;
-        if constexpr ((FEAT & FEAT_SCHEME) != 0) {  // moving wall: u -> 2 u_w - u
-          const T uw2 = T(2) * (yb == 0 ? ph.uw_lo : ph.uw_hi);
-          am.ux += uw2; am.mux += uw2 * m0; am.rux += uw2 * rho;
-        }
-        bm.muy = -b.muy; bm.ruy = -b.ruy;
-        s_u4[sg2][t] = am;
-        s_u2[sg2][t] = bm;
+      if (WALLS && (yb == 0 || (!R3 && yb == ny - 1)))
+        image(a, b, m0, rho, yb == 0 ? ph.uw_lo : ph.uw_hi, R3 ? slot(0, I + 1) : slot(yb == 0 ? -1 : ny, 0));
+    } else if (WALLS && R3 && yb == ny && ulane) {
+      // above the upper wall: the image of row ny - 1 (yn - 2, stage C's row)
+      U4<T> a = s_u4[slot(yb - 1, I + 1)][pt];
+      U2<T> b = s_u2[slot(yb - 1, I + 1)][pt];
+      if constexpr (XW) {  // (stored negated beyond an x-wall)
+        a.ux = xmir ? -a.ux : a.ux; a.uy = xmir ? -a.uy : a.uy;
+        a.mux = xmir ? -a.mux : a.mux; a.rux = xmir ? -a.rux : a.rux;
+        b.muy = xmir ? -b.muy : b.muy; b.ruy = xmir ? -b.ruy : b.ruy;
       }
+      image(a, b, rC.phi * rho0 + rC.dm0, rho0 + rC.drho, ph.uw_hi, slot(yb, I + 2));
     }
     __syncthreads();
     if (sizeof(S) != 4) __builtin_amdgcn_s_setprio(0);  // stage C after them
@@ -754,20 +794,21 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
     // ---------------- stage C: collide row yn-2 ----------------
     const int yo = yn - 2;
     if (yo >= y0 && olane) {
-      const int uo = slot4(yo), us = slot4(yo - 1), un = slot4(yo + 1);
+      const int uo = slot(yo, I + 1), us = slot(yo - 1, I), un = slot(yo + 1, I + 2);
       VelAround<T> v;
-      v.C = s_u4[uo][tc];
-      v.E = s_u4[uo][tr]; v.W = s_u4[uo][tl];
-      v.N = s_u4[un][tc]; v.S = s_u4[us][tc];
-      v.NE = s_u4[un][tr]; v.NW = s_u4[un][tl];
-      v.SE = s_u4[us][tr]; v.SW = s_u4[us][tl];
-      v.bN = s_u2[un][tc]; v.bS = s_u2[us][tc];
-      v.bNE = s_u2[un][tr]; v.bNW = s_u2[un][tl];
-      v.bSE = s_u2[us][tr]; v.bSW = s_u2[us][tl];
+      v.C = s_u4[uo][pc];
+      v.E = s_u4[uo][pr]; v.W = s_u4[uo][pl];
+      v.N = s_u4[un][pc]; v.S = s_u4[us][pc];
+      v.NE = s_u4[un][pr]; v.NW = s_u4[un][pl];
+      v.SE = s_u4[us][pr]; v.SW = s_u4[us][pl];
+      v.bN = s_u2[un][pc]; v.bS = s_u2[us][pc];
+      v.bNE = s_u2[un][pr]; v.bNW = s_u2[un][pl];
+      v.bSE = s_u2[us][pr]; v.bSW = s_u2[us][pl];
       T o9[9];
-      Derivs<T> d;
-      derivs_of<FEAT>(v, rC, ph, [&](int i) { return s_u2[uo][i == 0 ? tc : (i == 1 ? tr : tl)]; }, d);
-      collide_of<FEAT>(d, rC, v.C.ux, v.C.uy, bOld[0], bOld[1], ph, o9);
+      T Ca, Cb, Cc;
+      penalty_of<FEAT>(v, rC, ph, [&](int i) { return s_u2[uo][i == 0 ? pc : (i == 1 ? pr : pl)]; }, Ca,
+                       Cb, Cc);
+      collide_of<FEAT>(Ca, Cb, Cc, rC, v.C.ux, v.C.uy, bOld[0], bOld[1], ph, o9);
       auto store_row = [&](T (&o)[9], T ph_n, T dph_n, int r) {
         stored<S, T, SHIFT, FEAT>(o, ph_n, dph_n, ph, [&](int i, S v) { bstore(v, dstr, xcb, poff(i, r)); });
       };
@@ -804,57 +845,32 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
     }
   };
 
-  // Software pipeline: the loads of row yn+PD are in flight while row yn is
-  // processed.  Unrolled by six so that the load buffers (period PD+1) and
-  // the three row states (period 3) are renamed instead of copied.
+  // Software pipeline: the loads of the next row are in flight while a row is
+  // processed (two rows ahead gained nothing at any occupancy).  Unrolled by
+  // six so that the load buffers (period two), the row states and the ring
+  // slots (period three) are renamed instead of copied.
   RowState<T> R0{}, R1{}, R2{};
   T b0[2] = {0, 0}, b1[2] = {0, 0};
-  if constexpr (PD == 1) {
-    RowIn<S, T> ia{}, ib{};
-    load_row(y0 - 2, ia);
-    for (int k = 0; k < nit; k += 6) {
-      load_row(y0 - 1 + k, ib);
-      body(k + 0, ia, R0, R2, R1, b0, b1);
-      if (k + 1 >= nit) break;
-      load_row(y0 + k, ia);
-      body(k + 1, ib, R1, R0, R2, b1, b0);
-      if (k + 2 >= nit) break;
-      load_row(y0 + 1 + k, ib);
-      body(k + 2, ia, R2, R1, R0, b0, b1);
-      if (k + 3 >= nit) break;
-      load_row(y0 + 2 + k, ia);
-      body(k + 3, ib, R0, R2, R1, b1, b0);
-      if (k + 4 >= nit) break;
-      load_row(y0 + 3 + k, ib);
-      body(k + 4, ia, R1, R0, R2, b0, b1);
-      if (k + 5 >= nit) break;
-      load_row(y0 + 4 + k, ia);
-      body(k + 5, ib, R2, R1, R0, b1, b0);
-    }
-  } else {
-    static_assert(PD == 2, "prefetch distance 1 or 2");
-    RowIn<S, T> ia{}, ib{}, ic{};
-    load_row(y0 - 2, ia);
-    load_row(y0 - 1, ib);
-    for (int k = 0; k < nit; k += 6) {
-      load_row(y0 + k, ic);
-      body(k + 0, ia, R0, R2, R1, b0, b1);
-      if (k + 1 >= nit) break;
-      load_row(y0 + 1 + k, ia);
-      body(k + 1, ib, R1, R0, R2, b1, b0);
-      if (k + 2 >= nit) break;
-      load_row(y0 + 2 + k, ib);
-      body(k + 2, ic, R2, R1, R0, b0, b1);
-      if (k + 3 >= nit) break;
-      load_row(y0 + 3 + k, ic);
-      body(k + 3, ia, R0, R2, R1, b1, b0);
-      if (k + 4 >= nit) break;
-      load_row(y0 + 4 + k, ia);
-      body(k + 4, ib, R1, R0, R2, b0, b1);
-      if (k + 5 >= nit) break;
-      load_row(y0 + 5 + k, ib);
-      body(k + 5, ic, R2, R1, R0, b1, b0);
-    }
+  RowIn<S, T> ia{}, ib{};
+  load_row(y0 - 2, ia);
+  for (int k = 0; k < nit; k += 6) {
+    load_row(y0 - 1 + k, ib);
+    body(std::integral_constant<int, 0>{}, k, ia, R0, R2, R1, b0, b1);
+    if (k + 1 >= nit) break;
+    load_row(y0 + k, ia);
+    body(std::integral_constant<int, 1>{}, k + 1, ib, R1, R0, R2, b1, b0);
+    if (k + 2 >= nit) break;
+    load_row(y0 + 1 + k, ib);
+    body(std::integral_constant<int, 2>{}, k + 2, ia, R2, R1, R0, b0, b1);
+    if (k + 3 >= nit) break;
+    load_row(y0 + 2 + k, ia);
+    body(std::integral_constant<int, 3>{}, k + 3, ib, R0, R2, R1, b1, b0);
+    if (k + 4 >= nit) break;
+    load_row(y0 + 3 + k, ib);
+    body(std::integral_constant<int, 4>{}, k + 4, ia, R1, R0, R2, b0, b1);
+    if (k + 5 >= nit) break;
+    load_row(y0 + 4 + k, ia);
+    body(std::integral_constant<int, 5>{}, k + 5, ib, R2, R1, R0, b1, b0);
   }
 }
 
@@ -864,14 +880,14 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
 // variant, whose extra state would spill heavily at four; with solid nodes
 // alone or with the force field and drag a few registers spill at four,
 // which measures faster than three).
-template <typename S, typename T, bool SHIFT, bool WALLS, int FEAT, int NT, int PD = 1,
+template <typename S, typename T, bool SHIFT, bool WALLS, int FEAT, int NT,
           int WPE = (sizeof(T) == 4 ? (((FEAT & FEAT_MASK) && (FEAT & (FEAT_DYNPHI | FEAT_SCHEME))) ? 3 : 4) : 2)>
 __global__ void __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(WPE)))
 vanse_step_kernel(StepGeom g, StepPhys<T> ph) {
   __shared__ StepLds<T, NT> lds;
   const int tile = xcd_tile(int(blockIdx.x), int(gridDim.x));
-  step_tile<S, T, SHIFT, WALLS, FEAT, NT, PD>(g, ph, tile % g.strips, tile / g.strips, lds);
+  step_tile<S, T, SHIFT, WALLS, FEAT, NT>(g, ph, tile % g.strips, tile / g.strips, lds);
 }
 
 // Many independent lattices per launch.  Entry xcd_tile(b) of the tile map
@@ -908,7 +924,7 @@ vanse_batch_step_kernel(const BatchEntry<T>* __restrict__ entries,
   // a private copy, as the one-lattice kernel's argument (read through the
   // table the parameters could alias the stores as far as the compiler knows)
   const StepPhys<T> ph = e.ph;
-  step_tile<S, T, SHIFT, WALLS, FEAT, NT, 1>(g, ph, local % g.strips, local / g.strips, lds);
+  step_tile<S, T, SHIFT, WALLS, FEAT, NT>(g, ph, local % g.strips, local / g.strips, lds);
 }
 
 }  // namespace vanse_dev

@@ -203,7 +203,7 @@ vanse_tile_kernel(StepGeom g, StepPhys<T> ph, int walls, int steps) {
         }
       } else {
         T m0, rho;
-        velocity_of<FEAT>(a, r, ffx, ffy, ph, u, v, Fx, Fy, m0, rho);
+        velocity_of<FEAT>(a, r, [&](T& fx, T& fy) { fx = ffx; fy = ffy; }, ph, u, v, Fx, Fy, m0, rho);
       }
       auto put = [&](int at, T sg) {
         L.u[at] = {sg * u.ux, sg * u.uy};
@@ -227,7 +227,7 @@ vanse_tile_kernel(StepGeom g, StepPhys<T> ph, int walls, int steps) {
       if constexpr (PAIRS) {
         // (rows below m, here c and above n, as derivs2_of; in FP64 row by row)
         auto part = [] { if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0); };
-        Derivs<T> d;
+        Derivs2<T> d;
         const Pair<T> uc = L.u[t];
         {
           const Pair<T> cE = L.u[e], cW = L.u[w];
@@ -314,7 +314,11 @@ vanse_tile_kernel(StepGeom g, StepPhys<T> ph, int walls, int steps) {
           d.ruy_y = stencil_dy(pN.b, pS.b, pNE.b, pNW.b, pSE.b, pSW.b);
         }
         __builtin_amdgcn_sched_barrier(0);
-        collide_of<FEAT>(d, r, uc.a, uc.b, Fx, Fy, ph, o9);
+        T Ca, Cb, Cc;
+        const T rho = ph.rho0 + r.drho, X = ph.kappa * r.rphi;
+        penalty20(d, ph.kappa, ph.kappa - r.phi, rho, X, Ca, Cb, Cc);
+        if (DYN) Ca -= T(2) * X * rho * r.dphi;
+        collide_of<FEAT>(Ca, Cb, Cc, r, uc.a, uc.b, Fx, Fy, ph, o9);
         stored<S, T, SHIFT, FEAT>(o9, phi, r.dphi, ph, [&](int i, S x) { out[i] = x; });
       }
     }
