@@ -465,16 +465,16 @@ int fused_rows(const vanse_lattice* h) {
 }
 
 // The instance of the tile kernel for single steps, or -1: the plain step with
-// any of the force field, the drag, solid nodes and walls in x (those with an
-// absent flag plane, which reads as zero), or a void fraction that moves now.
+// any of the force field, the drag, solid nodes and walls in x (which need no
+// flags there), or a void fraction that moves now.
 // (A moving phi that is held constant adds nothing to the step: its lattices
 // take the instance without it.)
 int tile_inst(const vanse_lattice* h) {
   const int f = feat_of(h);
   if ((f & FEAT_SCHEME) || h->nee_lo || h->nee_hi) return -1;
   const int fd = (h->d.has_force_field ? FEAT_FORCE : 0) | (h->d.has_drag ? FEAT_DRAG : 0);
-  if (h->phin_set) return (f & FEAT_MASK) ? -1 : FEAT_MOVING;
-  if (f & FEAT_MASK) return fd ? (FEAT_MASK | FEAT_FORCE | FEAT_DRAG) : FEAT_MASK;
+  if (h->phin_set) return h->d.has_mask ? -1 : FEAT_MOVING;
+  if (h->d.has_mask) return fd ? (FEAT_MASK | FEAT_FORCE | FEAT_DRAG) : FEAT_MASK;
   return fd;
 }
 
@@ -490,19 +490,30 @@ long long tile_blocks(const vanse_lattice* h, int steps) {
   return (long long)((h->d.nx + ox - 1) / ox) * ((h->d.ny + oy - 1) / oy);
 }
 
+// Estimated time of a two-step launch of the tile kernel: 6.5 us and 6.2 us a
+// round of tiles (one workgroup fills a CU's registers); with solid nodes 6.5 us
+// a round in FP32 and 8.4 in FP64.  Measured: 19.3 us at 2.25 rounds (512 x 512
+// FP32), 43.4 at 6.6 (900 x 900), 28.4 at 3.5 (512 x 512 FP64); with solid nodes
+// 34.2 at 4.25 (700 x 737 FP32) and at 3.5 (512 x 512 FP64).
+double tile_pair_us(const vanse_lattice* h) {
+  const double rounds = (double)tile_blocks(h, 2) / device_cus();
+  return 6.5 + (!h->d.has_mask ? 6.2 : h->d.precision == VANSE_F64 ? 8.4 : 6.5) * rounds;
+}
+
 // Steps per launch of the tile kernel for n single steps, or 0 for the row
 // sweep (which also serves a launch shape that the caller chose).  As many as
-// leave every CU at most one tile (one workgroup fills a CU's registers), up
-// to four: more steps share a launch, but their tiles output less and
-// recompute more.  Where two steps need more than one round of tiles, they
-// still win while the rounds are few -- the line lies where both sides
-// measured alike, from 512 x 512 and 1003 x 777 nodes (us per step, sweep
-// against tiles): FP32 10.8/9.6 at 576 tiles, 18.5/21.8 at 1656; FP64 16.7/14.3
-// at 888, 27.3/34.6 at 2576; walls in x with a force field or drag, whose sweep
-// runs three waves per SIMD and carries a moving phi's planes, FP16 29.4/24.5
-// at 1656.  A single step (also a hand-over of phi, which takes one per call)
-// of several rounds is no faster than the sweep in FP32, and up to two rounds
-// in FP64.
+// leave every CU at most one tile, up to four: more steps share a launch, but
+// their tiles output less and recompute more.  Where two steps need more than
+// one round of tiles, the estimates decide: a sweep takes its rows and four
+// more, each, in us, 2.0 (the plain step, the force field, the drag), 2.4 (FP32)
+// or 2.7 (FP64) with solid nodes, 2.6 or 2.7 with walls in x, and with both walls
+// in x and a force field or drag (the instance that carries a moving phi's
+// planes) 3.4 or 3.1.  Measured (us per step, sweep/tiles): FP32 512 x 512 10.8/9.6, 700 x 700
+// 13.5/13.6; FP64 512 x 512 16.7/14.2, 700 x 700 21.1/23.8; closed box FP32 700 x
+// 700 16.9/13.6, 1000 x 1000 24.1/27.2, with drag 30.2/28.2; solid nodes FP64 512
+// x 512 21.5/17.1, 500 x 500 16.0/17.7.  A single step (also a hand-over of phi,
+// which takes one per call) of several rounds is no faster than the sweep in
+// FP32, and up to two rounds in FP64.
 int tile_steps(const vanse_lattice* h, int64_t n) {
   if (!h->tiling_default || tile_inst(h) < 0) return 0;
   const int cus = device_cus();
@@ -510,21 +521,23 @@ int tile_steps(const vanse_lattice* h, int64_t n) {
   if (n == 1 || h->phin_set) return tile_blocks(h, 1) <= (f64 ? 2 : 1) * cus ? 1 : 0;
   for (int k = 4; k >= 2; --k)
     if (tile_blocks(h, k) <= cus) return k;
-  const bool slow_sweep = feat_of(h) == (FEAT_MASK | FEAT_MOVING);
-  const int rounds = slow_sweep ? 7 : (f64 ? 4 : 3);
-  return tile_blocks(h, 2) <= (long long)rounds * cus ? 2 : 0;
+  const int f = feat_of(h);
+  const double row = f == (FEAT_MASK | FEAT_MOVING) ? (f64 ? 3.1 : 3.4) : !(f & FEAT_MASK) ? 2.0 : f64 ? 2.7 : h->d.has_mask ? 2.4 : 2.6;
+  return tile_pair_us(h) < 2.0 * row * (h->rows + 4) ? 2 : 0;
 }
 
 // Steps per launch of the tile kernel for pairs of steps (4 or 2), or 0 for
 // the two-step sweep (which also serves rows per workgroup that the caller
-// chose): by the same rule.  The sweep's twelve rows of pipeline take 9-13 us
-// a step however small the lattice.
+// chose): as above, the sweep's rows and twelve more (its pipeline) taking
+// 1.45 us (FP32) or 1.75 us (FP64) each, 2.0 or 2.3 with solid nodes.  Measured
+// (us per step, sweep/tiles): FP32 512 x 512 11.6/9.8, FP64 15.9/14.7; solid
+// nodes FP32 700 x 700 17.0/14.2, FP64 512 x 512 20.8/15.5.
 int tile_pair_steps(const vanse_lattice* h) {
   if (h->rows2 > 0 || tile_pair_inst(h) < 0) return 0;
-  const int cus = device_cus();
-  if (!h->phin2_set && tile_blocks(h, 4) <= cus) return 4;
-  const int half_rounds = (h->d.precision == VANSE_F64 || h->d.has_mask) ? 8 : 5;
-  return 2 * tile_blocks(h, 2) <= (long long)half_rounds * cus ? 2 : 0;
+  if (!h->phin2_set && tile_blocks(h, 4) <= device_cus()) return 4;
+  const bool f64 = h->d.precision == VANSE_F64;
+  const double row = h->d.has_mask ? (f64 ? 2.3 : 2.0) : (f64 ? 1.75 : 1.45);
+  return tile_blocks(h, 2) <= device_cus() || tile_pair_us(h) < row * (fused_rows(h) + 12) ? 2 : 0;
 }
 
 // n steps with the tile kernel, at most k per launch, in units of `unit` steps
