@@ -1048,14 +1048,21 @@ static int upload(vanse_lattice* h, const UploadJob* jobs, int n, hipStream_t st
   return fail(VANSE_ERR_INVALID_ARG, "void-fraction values outside (0, 1]");
 }
 
+// Upload a void fraction over one that may be in use: into the spare plane
+// first, so that a field that is refused leaves the current one, then into its
+// own (whose address launches captured in a graph hold).
+static int upload_over(vanse_lattice* h, const double* phi, size_t plane, hipStream_t st) {
+  const UploadJob job = {phi, h->ws + h->L.spare, 1};
+  if (int rc = upload(h, &job, 1, st)) return rc;
+  HIP_TRY(hipMemcpyAsync(h->ws + plane, h->ws + h->L.spare, h->L.plane * arith_bytes(h), hipMemcpyDeviceToDevice, st));
+  return VANSE_OK;
+}
+
 int vanse_set_void_fraction(vanse_lattice* h, const double* phi, void* stream) {
   if (int rc = check_handle(h)) return rc;
   if (!phi) return fail(VANSE_ERR_INVALID_ARG, "phi is NULL");
   if (h->phin_set || h->phin2_set) return fail(VANSE_ERR_STATE, "phi(t+1) is pending; step first");
-  // into the spare plane: a field that is refused leaves the current one
-  const UploadJob job = {phi, h->ws + h->L.spare, 1};
-  if (int rc = upload(h, &job, 1, static_cast<hipStream_t>(stream))) return rc;
-  std::swap(h->L.phi, h->L.spare);
+  if (int rc = upload_over(h, phi, h->L.phi, static_cast<hipStream_t>(stream))) return rc;
   h->phi_set = true;
   h->version += 1;
   return VANSE_OK;
@@ -1067,8 +1074,9 @@ int vanse_set_void_fraction_next(vanse_lattice* h, const double* phi_next, void*
   if (!phi_next) return fail(VANSE_ERR_INVALID_ARG, "phi_next is NULL");
   if (!h->phi_set) return fail(VANSE_ERR_STATE, "void fraction not set");
   if (h->phin2_set) return fail(VANSE_ERR_STATE, "phi(t+1) and phi(t+2) are pending; step first");
+  hipStream_t st = static_cast<hipStream_t>(stream);
   const UploadJob job = {phi_next, h->ws + h->L.phin, 1};
-  if (int rc = upload(h, &job, 1, static_cast<hipStream_t>(stream))) return rc;
+  if (int rc = h->phin_set ? upload_over(h, phi_next, h->L.phin, st) : upload(h, &job, 1, st)) return rc;
   h->phin_set = true;
   h->version += 1;
   return VANSE_OK;
