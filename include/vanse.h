@@ -281,7 +281,7 @@ int vanse_observe_noalloc(vanse_lattice *h, double *out, void *stream);
 int vanse_residual(vanse_lattice *h, double *out, void *stream);
 
 /* Launch shape of the step kernel: threads per workgroup (64, 128, 256 or
- * 512; a workgroup owns threads-4 columns) and rows swept per workgroup
+ * 512; a workgroup owns at most threads-4 columns) and rows swept per workgroup
  * (>= 1).  threads = 0 or rows = 0 restores the size-based default, which on
  * lattices too small to fill the GPU replaces this row sweep by a kernel that
  * advances up to four steps per launch, with bitwise the same results (the
@@ -334,8 +334,9 @@ int vanse_stream_copy(vanse_lattice *h, int64_t n, void *stream);
  * Many independent lattices advanced together: every call to
  * vanse_batch_step launches ONE kernel per time step (or per two, see
  * vanse_batch_create_ex) whose workgroups cover the tiles of all member
- * lattices (tile = strip of threads-4 columns x `rows` rows of one lattice).  Each member's arithmetic is exactly that of
- * vanse_step (results are bitwise identical).  Members must share precision,
+ * lattices (tile = strip of at most threads-4 columns x `rows` rows of one
+ * lattice).  Each member's arithmetic is exactly that of vanse_step (results
+ * are bitwise identical).  Members must share precision,
  * boundary types, force field, drag, mask and scheme variant (VANSE_ERR_INVALID_ARG
  * otherwise), be fully set up, and stay alive
  * while the batch exists.  The batch keeps a table of the members'
@@ -348,8 +349,8 @@ int vanse_stream_copy(vanse_lattice *h, int64_t n, void *stream);
 typedef struct vanse_batch vanse_batch;
 
 /* Workspace bytes for a batch of n lattices with the given workgroup width
- * (64, 128 or 256) and rows per workgroup (0: about two rounds of resident
- * workgroups over the batch). */
+ * (64, 128 or 256) and rows per workgroup (0: one round of resident
+ * workgroups over the batch if that takes at most 24 rows, else about two). */
 int vanse_batch_workspace_bytes(vanse_lattice *const *lats, int n, int threads,
                                 int rows, size_t *bytes);
 int vanse_batch_create(vanse_lattice *const *lats, int n, int threads, int rows,
@@ -364,7 +365,7 @@ int vanse_batch_destroy(vanse_batch *b);
  * workgroup of 2 x threads lanes, at most the half width of that instance
  * (256 in FP32 arithmetic, 128 in FP64, half that for solid nodes with the
  * drag and for the Appendix B equilibrium; VANSE_ERR_UNSUPPORTED beyond), a
- * tile is a strip of threads-10 columns, and rows = 0 gives about four
+ * tile is a strip of at most threads-10 columns, and rows = 0 gives about four
  * rounds of resident workgroups.  Each member's results are bitwise those
  * of stepping it alone with two steps per launch; an odd step count ends
  * with one step of each member on its own. */

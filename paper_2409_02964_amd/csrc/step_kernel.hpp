@@ -513,9 +513,10 @@ __device__ __forceinline__ void collide_of(T Ca, T Cb, T Cc, const RowState<T>& 
 // one register per ring; slots by the row modulo four cost 33 of 285 vector
 // instructions a row in address arithmetic.  2 to 11% faster (us per step, 2048 x
 // 2048: plain 144 -> 143, drag and force field 167 -> 164, moving phi 167 -> 151,
-// model B 169 -> 155).  FP32: four rows, the slot the row modulo four, since
-// the three-row ring gained nothing there and cost the instances with solid
-// nodes 1-8%.
+// model B 169 -> 155).  FP32: four rows, the slot the row modulo four.  Three
+// rows save 20 of 300 vector instructions a row there too, but took 1-8% longer
+// with solid nodes, 1-2.5% without in FP16 storage and 0-3% in FP32 (2048 x 2048,
+// drag, FP16: 50.0 -> 51.0; moving phi, FP32, 1777 x 1303: 38.3 -> 39.6).
 template <typename T>
 constexpr bool ring3() { return sizeof(T) == 8; }
 template <typename T, int NT>

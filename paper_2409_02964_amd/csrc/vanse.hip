@@ -508,12 +508,12 @@ double tile_pair_us(const vanse_lattice* h) {
 // more, each, in us, 2.0 (the plain step, the force field, the drag), 2.4 (FP32)
 // or 2.7 (FP64) with solid nodes, 2.6 or 2.7 with walls in x, and with both walls
 // in x and a force field or drag (the instance that carries a moving phi's
-// planes) 3.4 or 3.1.  Measured (us per step, sweep/tiles): FP32 512 x 512 10.8/9.6, 700 x 700
-// 13.5/13.6; FP64 512 x 512 16.7/14.2, 700 x 700 21.1/23.8; closed box FP32 700 x
-// 700 16.9/13.6, 1000 x 1000 24.1/27.2, with drag 30.2/28.2; solid nodes FP64 512
-// x 512 21.5/17.1, 500 x 500 16.0/17.7.  A single step (also a hand-over of phi,
-// which takes one per call) of several rounds is no faster than the sweep in
-// FP32, and up to two rounds in FP64.
+// planes) 3.4 or 3.1.  Measured (us per step, sweep/tiles): FP32 512 x 512
+// 10.8/9.6, 700 x 700 13.5/13.6; FP64 512 x 512 16.7/14.2, 700 x 700 21.1/23.8;
+// closed box FP32 700 x 700 16.9/13.6, 1000 x 1000 24.1/27.2, with drag
+// 30.2/28.2; solid nodes FP64 512 x 512 21.5/17.1, FP16 700 x 737 16.2/17.0.  A
+// single step (also a hand-over of phi, which takes one per call) of several
+// rounds is no faster than the sweep in FP32, and up to two rounds in FP64.
 int tile_steps(const vanse_lattice* h, int64_t n) {
   if (!h->tiling_default || tile_inst(h) < 0) return 0;
   const int cus = device_cus();
@@ -522,7 +522,11 @@ int tile_steps(const vanse_lattice* h, int64_t n) {
   for (int k = 4; k >= 2; --k)
     if (tile_blocks(h, k) <= cus) return k;
   const int f = feat_of(h);
-  const double row = f == (FEAT_MASK | FEAT_MOVING) ? (f64 ? 3.1 : 3.4) : !(f & FEAT_MASK) ? 2.0 : f64 ? 2.7 : h->d.has_mask ? 2.4 : 2.6;
+  const double row = f == (FEAT_MASK | FEAT_MOVING) ? (f64 ? 3.1 : 3.4)
+                     : !(f & FEAT_MASK)             ? 2.0
+                     : f64                          ? 2.7
+                     : h->d.has_mask                ? 2.4
+                                                    : 2.6;
   return tile_pair_us(h) < 2.0 * row * (h->rows + 4) ? 2 : 0;
 }
 
@@ -1576,15 +1580,28 @@ int batch_layout(vanse_lattice* const* lats, int n, int threads, int rows, int f
   }
   int r = rows;
   if (r == 0) {
-    // about two rounds of resident workgroups over the whole batch for one
-    // step per launch, four for two (measured on 256 lattices of side 32 to
-    // 512: shorter tiles balance the uneven lattices better), but at least
-    // 32 rows for two (each two-step tile sweeps 11 rows beyond its own)
+    // One step per launch: the lowest tiles that make one round of resident
+    // workgroups, if that takes at most 24 rows -- a small batch is bound by the
+    // latency of its tiles' rows (and five more), which a second round doubles --,
+    // else about two rounds of at least 8 rows, which is no worse there and
+    // balances uneven lattices.  Measured (us per step, at least 8 rows / one
+    // round; six or so lattices of sides up to L, FP16, 64 lanes): L = 150
+    // 13.6/5.2, 256 12.7/9.0, 700 20.7/19.5, 1500 53.3/50.8 (20 rows); 2048, where
+    // one round takes 34 rows, 18 rows 107, 36 rows 111.  FP32 alike; FP64 L = 150
+    // 14.2/5.9, 700 43.2/40.2.  Two steps: four rounds (measured on 256 lattices of
+    // side 32 to 512: shorter tiles balance the uneven lattices better), but at
+    // least 32 rows (each tile sweeps 11 rows beyond its own).
     const int rounds = fuse == 2 ? 4 : 2;
     const long long slots = (long long)device_cus() * batch_per_cu(d0.precision, threads, fuse);
-    r = (int)((strip_rows + rounds * slots - 1) / (rounds * slots));
-    const int rmin = fuse == 2 ? 32 : 8;
-    if (r < rmin) r = rmin;
+    r = (int)std::max<long long>((strip_rows + rounds * slots - 1) / (rounds * slots), fuse == 2 ? 32 : 8);
+    for (int q = 1; fuse == 1 && q <= 24; ++q) {
+      long long tiles = 0;
+      for (int k = 0; k < n; ++k) {
+        const vanse_desc& d = lats[k]->d;
+        tiles += (long long)((d.nx + out_w - 1) / out_w) * ((d.ny + q - 1) / q);
+      }
+      if (tiles <= slots) { r = q; break; }
+    }
   }
   rows_out->assign(n, r);
   first_out->assign(n, 0);
