@@ -365,8 +365,8 @@ int vanse_batch_destroy(vanse_batch *b);
  * workgroup of 2 x threads lanes, at most the half width of that instance
  * (256 in FP32 arithmetic, 128 in FP64, half that for solid nodes with the
  * drag and for the Appendix B equilibrium; VANSE_ERR_UNSUPPORTED beyond), a
- * tile is a strip of at most threads-10 columns, and rows = 0 gives about four
- * rounds of resident workgroups.  Each member's results are bitwise those
+ * tile is a strip of at most threads-10 columns, and rows = 0 gives one round
+ * of resident workgroups if that takes at most 31 rows, else about four.  Each member's results are bitwise those
  * of stepping it alone with two steps per launch; an odd step count ends
  * with one step of each member on its own. */
 int vanse_batch_workspace_bytes_ex(vanse_lattice *const *lats, int n, int threads,

@@ -856,10 +856,10 @@ struct HostRecord {
 }  // namespace
 
 // Scratch of vanse_observe_noalloc: the FP64 block partials of one read-out
-// (one record per 256-column block of a row, at most kScratchBlocks), the
-// chunk records of the first reduction level and the final record.  Each
-// device holds its own copy for the life of the process; every call on a
-// device overwrites it, so calls that overlap on one device race.
+// (at most kScratchBlocks; read_shape gives about 2048), the chunk records of
+// the first reduction level and the final record.  Each device holds its own
+// copy for the life of the process; every call on a device overwrites it, so
+// calls that overlap on one device race.
 constexpr long long kScratchBlocks = 1LL << 17;
 static __device__ __align__(256) double scratch[(kScratchBlocks + 1024 + 1) * NOBS];
 
@@ -1580,21 +1580,21 @@ int batch_layout(vanse_lattice* const* lats, int n, int threads, int rows, int f
   }
   int r = rows;
   if (r == 0) {
-    // One step per launch: the lowest tiles that make one round of resident
-    // workgroups, if that takes at most 24 rows -- a small batch is bound by the
-    // latency of its tiles' rows (and five more), which a second round doubles --,
-    // else about two rounds of at least 8 rows, which is no worse there and
-    // balances uneven lattices.  Measured (us per step, at least 8 rows / one
-    // round; six or so lattices of sides up to L, FP16, 64 lanes): L = 150
+    // The lowest tiles that make one round of resident workgroups, if that takes
+    // at most 24 rows (31 with two steps per launch) -- a small batch is bound by
+    // the latency of its tiles' rows and of those that fill the pipeline (five, or
+    // twelve), which a second round doubles.  Else about two rounds of at least 8
+    // rows (four of at least 32), which is no worse there and balances uneven
+    // lattices.  Measured (us per step, the second rule / one round; six or so
+    // lattices of sides up to L, FP16, 64 lanes): one step per launch L = 150
     // 13.6/5.2, 256 12.7/9.0, 700 20.7/19.5, 1500 53.3/50.8 (20 rows); 2048, where
-    // one round takes 34 rows, 18 rows 107, 36 rows 111.  FP32 alike; FP64 L = 150
-    // 14.2/5.9, 700 43.2/40.2.  Two steps: four rounds (measured on 256 lattices of
-    // side 32 to 512: shorter tiles balance the uneven lattices better), but at
-    // least 32 rows (each tile sweeps 11 rows beyond its own).
+    // one round takes 34 rows, 18 rows 107, 36 rows 111; two steps 150 21.0/8.0,
+    // 256 21.1/10.2, 700 22.9/16.9 (12 rows).  FP32 alike; FP64 150 14.2/5.9, 700
+    // 43.2/40.2, two steps 29.7/11.2 and 35.5/30.9 (24 rows).
     const int rounds = fuse == 2 ? 4 : 2;
     const long long slots = (long long)device_cus() * batch_per_cu(d0.precision, threads, fuse);
     r = (int)std::max<long long>((strip_rows + rounds * slots - 1) / (rounds * slots), fuse == 2 ? 32 : 8);
-    for (int q = 1; fuse == 1 && q <= 24; ++q) {
+    for (int q = fuse == 2 ? 4 : 1; q <= (fuse == 2 ? 31 : 24); ++q) {
       long long tiles = 0;
       for (int k = 0; k < n; ++k) {
         const vanse_desc& d = lats[k]->d;
