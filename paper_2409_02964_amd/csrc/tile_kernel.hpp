@@ -269,10 +269,14 @@ vanse_tile_kernel(StepGeom g, StepPhys<T> ph, int walls, int steps) {
 #pragma unroll
           for (int i = 0; i < 9; ++i) o9[i] = T(0);
         }
-        if (DYN && (!second || SHIFT)) o9[0] -= ((SHIFT && second) ? ph.scale : T(1)) * (ph.rho0 * r.dphi);
+        const T drest = DYN ? ph.rho0 * r.dphi : T(0);
+        if (DYN && !second) o9[0] -= drest;
         if (second && SHIFT) {  // already scaled
+          // (FP16: product, difference and conversion in one instruction that
+          // rounds once, as the sweep's code does)
+          out[0] = static_cast<S>(DYN ? o9[0] - ph.scale * drest : o9[0]);
 #pragma unroll
-          for (int i = 0; i < 9; ++i) out[i] = static_cast<S>(o9[i]);
+          for (int i = 1; i < 9; ++i) out[i] = static_cast<S>(o9[i]);
         } else if (second) {
           stored<S, T, false, 0>(o9, r.phi, T(0), ph, [&](int i, S x) { out[i] = x; });
         }

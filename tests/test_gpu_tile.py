@@ -157,3 +157,35 @@ def test_moving_void_fraction(precision, bc_y, options, spp):
     for k, (a, b) in enumerate(zip(run(False), run(True))):
         assert torch.isfinite(a).all()
         assert torch.equal(a, b), (k, (a - b).abs().max().item())
+
+
+@pytest.mark.parametrize("spp", [1, 2])
+@pytest.mark.parametrize("precision", ["f32s", "f16s"])
+def test_moving_void_fraction_over_many_nodes(precision, spp):
+    """As above over enough nodes and steps to meet values near the middle of
+    two FP16 numbers, where rounding twice differs from rounding once."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2409_02964_amd.vanse import Lattice
+    nx, ny, steps = 187, 283, 24
+    y, x = np.mgrid[0:ny, 0:nx]
+    phis = [torch.from_numpy(0.6 + 0.3 * np.sin(2 * np.pi * (x - 0.02 * t) / nx) * np.sin(2 * np.pi * (y - 0.02 * t) / ny)).cuda()
+            for t in range(steps + 1)]
+    out = []
+    for swept in (False, True):
+        lat = Lattice(nx, ny, precision=precision, drag=True, dynamic_phi=True).set_params(0.3, RATES)
+        lat.set_body_force(1.5e-6, 0.0).set_steps_per_pass(spp, 5 if swept else 0)
+        if swept:
+            lat.set_tiling(64, 7)
+        lat.set_void_fraction(phis[0]).set_drag(phis[0] * (1 - phis[0]), (1e-2, 0.0)).init_equilibrium(1.0, 0.03, 0.015)
+        for t in range(0, steps, spp):
+            lat.set_drag(phis[t] * (1 - phis[t]), (1e-2, 0.0))
+            if spp == 2:
+                lat.set_void_fraction_next2(phis[t + 1], phis[t + 2], phis[t + 1] * (1 - phis[t + 1]), None)
+            else:
+                lat.set_void_fraction_next(phis[t + 1])
+            lat.step(spp)
+        out.append(lat.read_populations())
+    assert torch.isfinite(out[0]).all()
+    assert torch.equal(*out)
