@@ -512,15 +512,19 @@ double tile_pair_us(const vanse_lattice* h) {
 // 10.8/9.6, 700 x 700 13.5/13.6; FP64 512 x 512 16.7/14.2, 700 x 700 21.1/23.8;
 // closed box FP32 700 x 700 16.9/13.6, 1000 x 1000 24.1/27.2, with drag
 // 30.2/28.2; solid nodes FP64 512 x 512 21.5/17.1, FP16 700 x 737 16.2/17.0.  A
-// single step (also a hand-over of phi, which takes one per call) of several
-// rounds is no faster than the sweep in FP32, and up to two rounds in FP64.
+// launch of a single step (also a hand-over of phi, which takes one per call, and
+// what is left of a call after its fours: the number of launches is nsteps modulo
+// two) of several rounds is no faster than the sweep in FP32, and up to two rounds
+// in FP64.
 int tile_steps(const vanse_lattice* h, int64_t n) {
   if (!h->tiling_default || tile_inst(h) < 0) return 0;
   const int cus = device_cus();
   const bool f64 = h->d.precision == VANSE_F64;
-  if (n == 1 || h->phin_set) return tile_blocks(h, 1) <= (f64 ? 2 : 1) * cus ? 1 : 0;
+  const int single = tile_blocks(h, 1) <= (f64 ? 2 : 1) * cus ? 1 : 0;
+  if (n == 1 || h->phin_set) return single;
   for (int k = 4; k >= 2; --k)
     if (tile_blocks(h, k) <= cus) return k;
+  if (n < 4) return single;
   const int f = feat_of(h);
   const double row = f == (FEAT_MASK | FEAT_MOVING) ? (f64 ? 3.1 : 3.4)
                      : !(f & FEAT_MASK)             ? 2.0
@@ -528,6 +532,15 @@ int tile_steps(const vanse_lattice* h, int64_t n) {
                      : h->d.has_mask                ? 2.4
                                                     : 2.6;
   return tile_pair_us(h) < 2.0 * row * (h->rows + 4) ? 2 : 0;
+}
+
+// Of n single steps at k per launch, those to hand to run_tiles at once.  Where
+// k = 2 takes more than one round of tiles, a launch of one step may be the
+// sweep's (tile_steps): only fours go there, which two launches of two steps
+// take, and the rest follows singly.
+int64_t tile_share(const vanse_lattice* h, int64_t n, int k) {
+  if (h->phin_set) return std::min<int64_t>(n, 1);
+  return k == 2 && tile_blocks(h, 2) > device_cus() ? n - n % 4 : n;
 }
 
 // Steps per launch of the tile kernel for pairs of steps (4 or 2), or 0 for
@@ -742,7 +755,7 @@ int run_steps(vanse_lattice* h, int64_t n, hipStream_t st) {
   if (const int k = tile_steps(h, n)) {
     // (with a void fraction pending, the first step alone: the second, of a
     // two-step hand-over stepped singly, has inputs of its own)
-    const int64_t first = h->phin_set ? std::min<int64_t>(n, 1) : n;
+    const int64_t first = tile_share(h, n, k);
     if (int rc = run_tiles<S, T, SHIFT>(h, first, k, 1, st)) return rc;
     if (first > 0) hand_over1(h);
     return first < n ? run_steps<S, T, SHIFT>(h, n - first, st) : VANSE_OK;
