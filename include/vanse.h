@@ -26,7 +26,11 @@
  *  - A handle must not be used by two host threads at once.
  *  - The library allocates no device memory: all device state lives in a
  *    caller-owned workspace of vanse_workspace_bytes() bytes that must
- *    outlive the handle.
+ *    outlive the handle.  It takes one page (4 KB) of pinned host memory, for
+ *    records that the device writes for the host, at the first call that
+ *    checks a void fraction or returns observables (vanse_observe_noalloc
+ *    excepted) and keeps it until the process ends; without it, or when 64
+ *    such calls are under way, records are copied from the device.
  */
 #ifndef VANSE_H
 #define VANSE_H
@@ -264,10 +268,12 @@ int vanse_observe(vanse_lattice *h, double *out, void *stream);
  * the lattice workspace's scratch -- the FP64 block partials and the
  * reduction records live in a static device array of the library (about
  * 5.3 MB, held by every device the library runs on until the process ends).
- * Allocates nothing.  Limit: ceil(nx/256) * ny <= 131072 (for example 4096 x
- * 8192 or 8192 x 4096); larger lattices get VANSE_ERR_INVALID_ARG before any
- * device work.  Calls that overlap on one device share the array and race:
- * serialize them (one stream, or events).
+ * Allocates nothing (the record comes through the library's page of pinned
+ * host memory when another call has taken it, and is copied from the device
+ * otherwise).  Limit: ceil(nx/256) * ny <= 131072 (for example
+ * 4096 x 8192 or 8192 x 4096); larger lattices get VANSE_ERR_INVALID_ARG
+ * before any device work.  Calls that overlap on one device share the array
+ * and race: serialize them (one stream, or events).
  * `out` is HOST memory (4 doubles); synchronizes the stream; returns
  * VANSE_ERR_DIVERGED (after filling out) when out[3] > 0. */
 int vanse_observe_noalloc(vanse_lattice *h, double *out, void *stream);

@@ -828,9 +828,11 @@ dim3 field_grid(const vanse_lattice* h) { return dim3((h->d.nx + 255) / 256, h->
 // Small records that the device hands to the host (the flag of an upload, the
 // observables): 64 slots of 64 bytes in one page of pinned host memory, which
 // the device writes directly -- no copy between the kernel and the
-// synchronization.  The page is taken at the first use and kept; a call leases
-// a slot and gives it back when it returns, so calls from several threads, on
-// several streams and devices, each have one of their own.
+// synchronization.  The page is taken at the first call that may allocate and
+// kept until the process ends; a call leases a slot and gives it back when it
+// returns, so calls from several threads, on several streams and devices, each
+// have one of their own.  A call that gets none (all leased, or no page) has the
+// record written to device memory and copies it: it neither allocates nor waits.
 namespace {
 
 constexpr int kHostSlots = 64, kHostSlotBytes = 64;
@@ -838,32 +840,47 @@ std::mutex g_host_mu;
 char* g_host_page = nullptr;
 unsigned long long g_host_used = 0;
 
-struct HostRecord {
-  char* p = nullptr;
-  int slot = -1;
-  int get() {  // a zeroed record, or an error
-    {
-      std::lock_guard<std::mutex> lock(g_host_mu);
-      if (!g_host_page)
-        HIP_TRY(hipHostMalloc((void**)&g_host_page, kHostSlots * kHostSlotBytes, hipHostMallocPortable));
-      if (~g_host_used) {
-        slot = __builtin_ctzll(~g_host_used);
-        g_host_used |= 1ull << slot;
-        p = g_host_page + slot * kHostSlotBytes;
-      }
+class HostRecord {
+ public:
+  // may_allocate: take the page if there is none yet
+  explicit HostRecord(bool may_allocate) {
+    std::lock_guard<std::mutex> lock(g_host_mu);
+    if (!g_host_page && may_allocate) {
+      void* page = nullptr;
+      if (hipHostMalloc(&page, kHostSlots * kHostSlotBytes, hipHostMallocPortable) == hipSuccess)
+        g_host_page = static_cast<char*>(page);
+      else
+        (void)hipGetLastError();
     }
-    if (!p) HIP_TRY(hipHostMalloc((void**)&p, kHostSlotBytes, hipHostMallocPortable));  // all leased
-    memset(p, 0, kHostSlotBytes);
-    return VANSE_OK;
+    if (!g_host_page || !~g_host_used) return;
+    slot_ = __builtin_ctzll(~g_host_used);
+    g_host_used |= 1ull << slot_;
+    p_ = g_host_page + slot_ * kHostSlotBytes;
+    memset(p_, 0, kHostSlotBytes);
   }
+  // The slot for a launch that writes it (zeroed), or null if there is none
+  void* lend() {
+    lent_ = p_ != nullptr;
+    return p_;
+  }
+  // The launch is done (the stream has been waited for)
+  const volatile void* landed() {
+    lent_ = false;
+    return p_;
+  }
+  // A slot that a launch may still write (the wait for it failed) stays leased
   ~HostRecord() {
-    if (slot >= 0) {
-      std::lock_guard<std::mutex> lock(g_host_mu);
-      g_host_used &= ~(1ull << slot);
-    } else if (p) {
-      (void)hipHostFree(p);
-    }
+    if (slot_ < 0 || lent_) return;
+    std::lock_guard<std::mutex> lock(g_host_mu);
+    g_host_used &= ~(1ull << slot_);
   }
+  HostRecord(const HostRecord&) = delete;
+  HostRecord& operator=(const HostRecord&) = delete;
+
+ private:
+  char* p_ = nullptr;
+  int slot_ = -1;
+  bool lent_ = false;
 };
 
 }  // namespace
@@ -1037,20 +1054,27 @@ static int upload(vanse_lattice* h, const UploadJob* jobs, int n, hipStream_t st
     check = check || jobs[k].check;
   }
   const uint16_t* nbr = h->mask_set ? (const uint16_t*)(h->ws + h->L.nbr) : nullptr;
-  HostRecord rec;
-  if (check)
-    if (int rc = rec.get()) return rc;
+  unsigned long long* bad = reinterpret_cast<unsigned long long*>(h->ws + h->L.badcount);
+  HostRecord rec(check);
+  int* flag = check ? static_cast<int*>(rec.lend()) : nullptr;
+  const bool on_device = check && !flag;
+  if (on_device) {
+    flag = reinterpret_cast<int*>(bad);
+    HIP_TRY(hipMemsetAsync(flag, 0, sizeof(*flag), st));
+  }
   dim3 grid = field_grid(h);
   grid.z = (unsigned)n;
   if (h->d.precision == VANSE_F64)
-    hipLaunchKernelGGL(upload_fields<double>, grid, dim3(256), 0, st, J, h->d.nx, h->d.ny, h->L.pitch, nbr, (int*)rec.p);
+    hipLaunchKernelGGL(upload_fields<double>, grid, dim3(256), 0, st, J, h->d.nx, h->d.ny, h->L.pitch, nbr, flag);
   else
-    hipLaunchKernelGGL(upload_fields<float>, grid, dim3(256), 0, st, J, h->d.nx, h->d.ny, h->L.pitch, nbr, (int*)rec.p);
+    hipLaunchKernelGGL(upload_fields<float>, grid, dim3(256), 0, st, J, h->d.nx, h->d.ny, h->L.pitch, nbr, flag);
   HIP_TRY(hipGetLastError());
   if (!check) return VANSE_OK;
+  int wrong = 0;
+  if (on_device) HIP_TRY(hipMemcpyAsync(&wrong, flag, sizeof(wrong), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
-  if (*(volatile int*)rec.p == 0) return VANSE_OK;
-  unsigned long long* bad = reinterpret_cast<unsigned long long*>(h->ws + h->L.badcount);
+  if (!on_device) wrong = *static_cast<const volatile int*>(rec.landed());
+  if (wrong == 0) return VANSE_OK;
   for (int k = 0; k < n; ++k) {  // how many, of the first field that has any
     if (!jobs[k].check) continue;
     HIP_TRY(hipMemsetAsync(bad, 0, sizeof(*bad), st));
@@ -1372,20 +1396,25 @@ static int reduce_on_device(vanse_lattice* h, hipStream_t st) {
                        (double*)(h->ws + h->L.result), st);
 }
 
-// Reduce n partials to one record that the device writes into host memory
-// (synchronizes the stream).
-static int reduce_to_host(const double* in, long long n, double* mid, double* out, hipStream_t st) {
-  HostRecord rec;
-  if (int rc = rec.get()) return rc;
-  if (int rc = reduce_blocks(in, n, mid, (double*)rec.p, st)) return rc;
+// Reduce n partials to one record in host memory (synchronizes the stream): the
+// device writes it there, or, without a slot for it, into res to be copied.
+static int reduce_to_host(const double* in, long long n, double* mid, double* res, bool may_allocate, double* out,
+                          hipStream_t st) {
+  HostRecord rec(may_allocate);
+  double* to = static_cast<double*>(rec.lend());
+  if (int rc = reduce_blocks(in, n, mid, to ? to : res, st)) return rc;
+  if (!to) HIP_TRY(hipMemcpyAsync(out, res, NOBS * sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
-  for (int q = 0; q < NOBS; ++q) out[q] = ((volatile double*)rec.p)[q];
+  if (to) {
+    const volatile double* r = static_cast<const volatile double*>(rec.landed());
+    for (int q = 0; q < NOBS; ++q) out[q] = r[q];
+  }
   return VANSE_OK;
 }
 
 static int reduce_to_host(vanse_lattice* h, double* out, hipStream_t st) {
   return reduce_to_host((const double*)(h->ws + h->L.partials), read_shape(h->d.nx, h->d.ny).blocks,
-                        (double*)(h->ws + h->L.partials2), out, st);
+                        (double*)(h->ws + h->L.partials2), (double*)(h->ws + h->L.result), true, out, st);
 }
 
 int vanse_observe(vanse_lattice* h, double* out, void* stream) {
@@ -1416,7 +1445,8 @@ int vanse_observe_noalloc(vanse_lattice* h, double* out, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (int rc = moments_into(h, nullptr, nullptr, nullptr, nullptr, part, st, false)) return rc;
   double rec[NOBS];
-  if (int rc = reduce_to_host(part, read_shape(h->d.nx, h->d.ny).blocks, mid, rec, st)) return rc;
+  if (int rc = reduce_to_host(part, read_shape(h->d.nx, h->d.ny).blocks, mid, mid + 1024 * NOBS, false, rec, st))
+    return rc;
   for (int q = 0; q < 4; ++q) out[q] = rec[q];
   if (out[3] > 0) return fail(VANSE_ERR_DIVERGED, "%.0f nodes hold non-finite values at t = %lld", out[3], (long long)h->t);
   return VANSE_OK;
