@@ -616,6 +616,7 @@ int run_tiles(vanse_lattice* h, int64_t n, int k, int unit, hipStream_t st) {
     h->t += steps;
     if (s == 0) HIP_TRY(hipGetLastError());
   }
+  HIP_TRY(hipGetLastError());
   return VANSE_OK;
 }
 
@@ -732,6 +733,7 @@ int run_fused_pairs(vanse_lattice* h, int64_t pairs, hipStream_t st) {
     hand_over2(h);
     if (s == 0) HIP_TRY(hipGetLastError());
   }
+  HIP_TRY(hipGetLastError());
   return VANSE_OK;
 }
 

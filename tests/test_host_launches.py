@@ -36,3 +36,21 @@ for n in range(1, 30):
     got = steps_of(n, 64, 64, "f64")
     assert len(got) % 2 == n % 2 and "s" not in got and len(got) <= n // 4 + 2
 ''')
+
+
+def test_a_launch_that_fails_late_is_reported_by_its_call(tmp_path):
+    run(tmp_path, '''
+for nx, spp in ((64, 1), (64, 2), (2000, 1), (2000, 2)):   # tiles and sweeps
+    h = ready(lattice(nx, 64), nx, 64)
+    V.check(L.vanse_set_steps_per_pass(h, spp, 0))
+    fail_launch = lambda name, k: 0
+    V.check(L.vanse_step(h, 40, None))
+    n = len(launches)
+    assert n > 2
+    for k in (1, 2, n):
+        del launches[:]
+        fail_launch = lambda name, i: i == k
+        assert L.vanse_step(h, 40, None) == -3, (nx, spp, k)
+    fail_launch = lambda name, k: 0
+    del launches[:]
+''')
