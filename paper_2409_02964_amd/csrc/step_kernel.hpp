@@ -511,17 +511,24 @@ __device__ __forceinline__ void collide_of(T Ca, T Cb, T Cc, const RowState<T>& 
 // a multiple of three, so a row's slot is a constant of the code and, with an
 // element of room at either end, every LDS address an immediate offset from
 // one register per ring; slots by the row modulo four cost 33 of 285 vector
-// instructions a row in address arithmetic.  2 to 11% faster (us per step, 2048 x
+// instructions a row in address arithmetic.  Up to 11% faster (us per step, 2048 x
 // 2048: plain 144 -> 143, drag and force field 167 -> 164, moving phi 167 -> 151,
-// model B 169 -> 155).  FP32: four rows, the slot the row modulo four.  Three
+// model B 169 -> 155).  One instance keeps four rows, solid nodes with a moving phi
+// and periodic in y (walls in x with a force field or drag take it too): its
+// registers are all in use, and with three rows it spilled more of them and took
+// 3-5% longer (1500 x 1497, walls in x, drag: 106.1 us per step against 99.4).
+// FP32: four rows, the slot the row modulo four.  Three
 // rows save 20 of 300 vector instructions a row there too, but took 1-8% longer
 // with solid nodes, 1-2.5% without in FP16 storage and 0-3% in FP32 (2048 x 2048,
 // drag, FP16: 50.0 -> 51.0; moving phi, FP32, 1777 x 1303: 38.3 -> 39.6).
-template <typename T>
-constexpr bool ring3() { return sizeof(T) == 8; }
-template <typename T, int NT>
+template <typename T, bool WALLS, int FEAT>
+constexpr bool ring3() {
+  return sizeof(T) == 8 && (WALLS || FEAT != (FEAT_MASK | FEAT_DYNPHI | FEAT_FORCE | FEAT_DRAG));
+}
+template <typename T, bool WALLS, int FEAT, int NT>
 struct StepLds {
-  static constexpr int ROWS = ring3<T>() ? 3 : 4, LEN = NT + (ring3<T>() ? 2 : 0);
+  static constexpr bool R3 = ring3<T, WALLS, FEAT>();
+  static constexpr int ROWS = R3 ? 3 : 4, LEN = NT + (R3 ? 2 : 0);
   T rho[ROWS][LEN];      // delta-rho (stage A -> stage B)
   U4<T> u4[ROWS][LEN];   // (stage B -> stage C)
   U2<T> u2[ROWS][LEN];
@@ -531,7 +538,7 @@ struct StepLds {
 // row block `by` (rows by*rows .. +rows-1) of the lattice described by g.
 template <typename S, typename T, bool SHIFT, bool WALLS, int FEAT, int NT>
 __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& ph, int strip,
-                                          int by, StepLds<T, NT>& L) {
+                                          int by, StepLds<T, WALLS, FEAT, NT>& L) {
   auto& s_rho = L.rho;
   auto& s_u4 = L.u4;
   auto& s_u2 = L.u2;
@@ -567,7 +574,7 @@ __device__ __forceinline__ void step_tile(const StepGeom& g, const StepPhys<T>& 
   const bool xmir = xw && (xg < 0 || xg >= nx);
   const bool xlo = xw && c == 0, xhi = xw && c == nx - 1;
   // positions in the rings of this lane and of lane tc and its neighbours
-  constexpr bool R3 = ring3<T>();
+  constexpr bool R3 = ring3<T, WALLS, FEAT>();
   const int pt = R3 ? t + 1 : t, pc = R3 ? tc + 1 : tc;
   const int pl = R3 ? tc : max(tc - 1, 0), pr = R3 ? tc + 2 : min(tc + 1, NT - 1);
   constexpr unsigned SB = sizeof(S);
@@ -886,7 +893,7 @@ template <typename S, typename T, bool SHIFT, bool WALLS, int FEAT, int NT,
 __global__ void __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(WPE)))
 vanse_step_kernel(StepGeom g, StepPhys<T> ph) {
-  __shared__ StepLds<T, NT> lds;
+  __shared__ StepLds<T, WALLS, FEAT, NT> lds;
   const int tile = xcd_tile(int(blockIdx.x), int(gridDim.x));
   step_tile<S, T, SHIFT, WALLS, FEAT, NT>(g, ph, tile % g.strips, tile / g.strips, lds);
 }
@@ -911,7 +918,7 @@ __global__ void __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(WPE)))
 vanse_batch_step_kernel(const BatchEntry<T>* __restrict__ entries,
                         const int2* __restrict__ tile_map, int launch) {
-  __shared__ StepLds<T, NT> lds;
+  __shared__ StepLds<T, WALLS, FEAT, NT> lds;
   const int2 tm = tile_map[xcd_tile(int(blockIdx.x), int(gridDim.x))];
   const int k = tm.x;
   const BatchEntry<T>& e = entries[k];
