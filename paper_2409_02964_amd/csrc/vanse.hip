@@ -490,71 +490,99 @@ long long tile_blocks(const vanse_lattice* h, int steps) {
   return (long long)((h->d.nx + ox - 1) / ox) * ((h->d.ny + oy - 1) / oy);
 }
 
-// Estimated time of a two-step launch of the tile kernel: 6.5 us and 6.2 us a
-// round of tiles (one workgroup fills a CU's registers); with solid nodes 6.5 us
-// a round in FP32 and 8.4 in FP64.  Measured: 19.3 us at 2.25 rounds (512 x 512
-// FP32), 43.4 at 6.6 (900 x 900), 28.4 at 3.5 (512 x 512 FP64); with solid nodes
-// 34.2 at 4.25 (700 x 737 FP32) and at 3.5 (512 x 512 FP64).
-double tile_pair_us(const vanse_lattice* h) {
-  const double rounds = (double)tile_blocks(h, 2) / device_cus();
-  return 6.5 + (!h->d.has_mask ? 6.2 : h->d.precision == VANSE_F64 ? 8.4 : 6.5) * rounds;
+// Rounds of tiles (tiles per CU: one workgroup fills a CU's registers) up to which
+// a launch of the tile kernel is faster than the row sweep, by the sweep instance
+// that it replaces.  Tiles cost their number, about 6 us a round for two steps.  A
+// sweep costs the rows of its pipeline and those that it takes per workgroup, so
+// beyond one round the limit is a number of rounds and some more for every such
+// row.  The dearer the sweep's instance is, the higher: with solid nodes (whose flags
+// the tiles need too), for walls in x (which they need no flags for), and most of all
+// where the sweep carries a moving phi's planes that the tiles do without.  Walls in y
+// spare tiles the wrapped indices; FP64 tiles are smaller.  Measured: 64000 times of
+// both kernels on lattices of random sides, options and storages; the limits are
+// those that cost least, and 0.6% of the launches lose more than 4% to the sweep.
+// Tiles' time over the sweep's, medians up to one round, from there to the limit, and
+// from the limit to half as far again: two steps per launch, plain FP32 0.63 0.84
+// 1.15, FP64 0.64 0.75 1.09; solid nodes 0.53 0.76 1.05, 0.58 0.73 1.13; walls in x 0.51
+// 0.78 1.15, 0.53 0.75 1.11, with force field or drag 0.50 0.83 1.02, 0.50 0.78 1.05.
+// One step per launch, up to one round: plain FP32 periodic in y 1.02, with walls 0.86;
+// FP64 0.94, 0.83; solid nodes 0.80, 0.74; walls in x 0.76, 0.70.
+struct TileLimit {
+  double rounds, per_row;
+};
+struct TileRounds {
+  double one[2][2];     // one step per launch, [FP64][walls in y]
+  TileLimit two[2][2];  // two
+};
+constexpr TileRounds kTileRounds[] = {
+    // plain, force field, drag
+    {{{0, 1}, {1, 1}}, {{{1.25, 0.75}, {2, 0.625}}, {{1.5, 0.25}, {1.75, 0.5}}}},
+    // moving phi (handed over or held)
+    {{{1, 1.75}, {1, 1.75}}, {{{1.75, 0.625}, {3.5, 0.25}}, {{1.5, 0.625}, {4, 0}}}},
+    // solid nodes
+    {{{1, 2}, {1, 2}}, {{{1.75, 0.75}, {3, 0.5}}, {{1.25, 0.625}, {2, 0.5}}}},
+    // walls in x
+    {{{1, 2.75}, {2, 3}}, {{{2, 1}, {3, 1}}, {{1.5, 0.875}, {3, 0.75}}}},
+    // with a force field, drag or moving phi
+    {{{2.25, 6}, {3, 4}}, {{{2.5, 1.5}, {2.5, 1.5}}, {{2.25, 1}, {1.75, 1.125}}}},
+    // solid nodes, where the sweep carries a moving phi's planes
+    {{{2, 6}, {2, 2.75}}, {{{2.25, 1.25}, {3.5, 1.25}}, {{2, 0.5}, {1.75, 0.75}}}},
+};
+// The same for a pair of steps against the two-step sweep (whose pipeline is longer
+// and whose rows cost less): rounds alone.  Medians, FP32 and FP64: 0.44 0.79 1.10,
+// 0.42 0.69 1.18 (phi handed over 0.55 0.81 1.06, 0.49 0.75 1.10); solid nodes 0.37 0.67
+// 1.08, 0.37 0.62 1.06.
+constexpr double kTilePairRounds[][2][2] = {
+    {{2.75, 3}, {3, 4}},   // plain, drag
+    {{3, 3}, {4, 4}},      // force field
+    {{2, 2.5}, {3, 3}},    // phi handed over, alone
+    {{2.5, 3}, {3.5, 4}},  // with drag (with a force field as above)
+    {{4, 4}, {4, 5}},      // solid nodes
+};
+
+const TileRounds& tile_rounds_of(const vanse_lattice* h) {
+  const int f = feat_of(h);
+  const bool planes = f == (FEAT_MASK | FEAT_MOVING);
+  return kTileRounds[h->d.has_mask ? (planes ? 5 : 2) : planes ? 4 : (f & FEAT_MASK) ? 3 : f == FEAT_MOVING ? 1 : 0];
 }
 
 // Steps per launch of the tile kernel for n single steps, or 0 for the row
 // sweep (which also serves a launch shape that the caller chose).  As many as
 // leave every CU at most one tile, up to four: more steps share a launch, but
-// their tiles output less and recompute more.  Where two steps need more than
-// one round of tiles, the estimates decide: a sweep takes its rows and four
-// more, each, in us, 2.0 (the plain step, the force field, the drag), 2.4 (FP32)
-// or 2.7 (FP64) with solid nodes, 2.6 or 2.7 with walls in x, and with both walls
-// in x and a force field or drag (the instance that carries a moving phi's
-// planes) 3.4 or 3.1.  Measured (us per step, sweep/tiles): FP32 512 x 512
-// 10.8/9.6, 700 x 700 13.5/13.6; FP64 512 x 512 16.7/14.2, 700 x 700 21.1/23.8;
-// closed box FP32 700 x 700 16.9/13.6, 1000 x 1000 24.1/27.2, with drag
-// 30.2/28.2; solid nodes FP64 512 x 512 21.5/17.1, FP16 700 x 737 16.2/17.0.  A
-// launch of a single step (also a hand-over of phi, which takes one per call, and
-// what is left of a call after its fours: the number of launches is nsteps modulo
-// two) of several rounds is no faster than the sweep in FP32, and up to two rounds
-// in FP64.
+// their tiles output less and recompute more.  A hand-over of phi takes one step
+// per call.  What tile_share leaves of a call runs as single steps.
 int tile_steps(const vanse_lattice* h, int64_t n) {
   if (!h->tiling_default || tile_inst(h) < 0) return 0;
-  const int cus = device_cus();
-  const bool f64 = h->d.precision == VANSE_F64;
-  const int single = tile_blocks(h, 1) <= (f64 ? 2 : 1) * cus ? 1 : 0;
+  const long long cus = device_cus();
+  const int f64 = h->d.precision == VANSE_F64, wy = h->d.bc_y == VANSE_WALL;
+  const TileRounds& most = tile_rounds_of(h);
+  const int single = tile_blocks(h, 1) <= most.one[f64][wy] * cus ? 1 : 0;
   if (n == 1 || h->phin_set) return single;
-  for (int k = 4; k >= 2; --k)
-    if (tile_blocks(h, k) <= cus) return k;
+  for (int k = 4; k >= 3; --k)
+    if (tile_blocks(h, k) <= cus) return n == 2 ? single : k;
   if (n < 4) return single;
-  const int f = feat_of(h);
-  const double row = f == (FEAT_MASK | FEAT_MOVING) ? (f64 ? 3.1 : 3.4)
-                     : !(f & FEAT_MASK)             ? 2.0
-                     : f64                          ? 2.7
-                     : h->d.has_mask                ? 2.4
-                                                    : 2.6;
-  return tile_pair_us(h) < 2.0 * row * (h->rows + 4) ? 2 : 0;
+  const TileLimit two = most.two[f64][wy];
+  return tile_blocks(h, 2) <= std::max(two.rounds + two.per_row * h->rows, 1.0) * cus ? 2 : 0;
 }
 
-// Of n single steps at k per launch, those to hand to run_tiles at once.  Where
-// k = 2 takes more than one round of tiles, a launch of one step may be the
-// sweep's (tile_steps): only fours go there, which two launches of two steps
-// take, and the rest follows singly.
+// Of n single steps at k per launch, those to hand to run_tiles at once: with two
+// per launch only fours, which two launches take.  The number of launches is n
+// modulo two, so the others would be launches of one step, and those may be the
+// sweep's.
 int64_t tile_share(const vanse_lattice* h, int64_t n, int k) {
   if (h->phin_set) return std::min<int64_t>(n, 1);
-  return k == 2 && tile_blocks(h, 2) > device_cus() ? n - n % 4 : n;
+  return k == 2 ? n - n % 4 : n;
 }
 
 // Steps per launch of the tile kernel for pairs of steps (4 or 2), or 0 for
 // the two-step sweep (which also serves rows per workgroup that the caller
-// chose): as above, the sweep's rows and twelve more (its pipeline) taking
-// 1.45 us (FP32) or 1.75 us (FP64) each, 2.0 or 2.3 with solid nodes.  Measured
-// (us per step, sweep/tiles): FP32 512 x 512 11.6/9.8, FP64 15.9/14.7; solid
-// nodes FP32 700 x 700 17.0/14.2, FP64 512 x 512 20.8/15.5.
+// chose).
 int tile_pair_steps(const vanse_lattice* h) {
   if (h->rows2 > 0 || tile_pair_inst(h) < 0) return 0;
   if (!h->phin2_set && tile_blocks(h, 4) <= device_cus()) return 4;
-  const bool f64 = h->d.precision == VANSE_F64;
-  const double row = h->d.has_mask ? (f64 ? 2.3 : 2.0) : (f64 ? 1.75 : 1.45);
-  return tile_blocks(h, 2) <= device_cus() || tile_pair_us(h) < row * (fused_rows(h) + 12) ? 2 : 0;
+  const int f64 = h->d.precision == VANSE_F64, wy = h->d.bc_y == VANSE_WALL;
+  const int row = h->d.has_mask ? 4 : h->d.has_force_field ? 1 : !h->phin2_set ? 0 : h->d.has_drag ? 3 : 2;
+  return tile_blocks(h, 2) <= kTilePairRounds[row][f64][wy] * device_cus() ? 2 : 0;
 }
 
 // n steps with the tile kernel, at most k per launch, in units of `unit` steps

@@ -54,3 +54,62 @@ for nx, spp in ((64, 1), (64, 2), (2000, 1), (2000, 2)):   # tiles and sweeps
     fail_launch = lambda name, k: 0
     del launches[:]
 ''')
+
+
+def test_tiles_or_sweep_by_rounds(tmp_path):
+    """Which kernel a step takes beyond one round of tiles (and single steps): the
+    tile kernel where it measured faster, on either side of the limits."""
+    run(tmp_path, '''
+def kernel(n, nx, ny, precision, bc_x="periodic", bc_y="periodic", spp=1, hand=0, **has):
+    h = lattice(nx, ny, precision, bc_x, bc_y, **has)
+    if "mask" in has:
+        V.check(L.vanse_set_mask(h, field(nx * ny), None))
+    if "drag" in has:
+        V.check(L.vanse_set_drag(h, field(nx * ny), 0.0, 0.0, None))
+    ready(h, nx, ny)
+    V.check(L.vanse_set_steps_per_pass(h, spp, 0))
+    if hand:
+        args = [field(nx * ny) for _ in range(hand)]
+        if hand == 2:
+            V.check(L.vanse_set_void_fraction_next2(h, *args, None, None, None, None))
+        else:
+            V.check(L.vanse_set_void_fraction_next(h, *args, None))
+    launches.clear()
+    V.check(L.vanse_step(h, n, None))
+    kinds = {"tiles" if "tile_kernel" in name else "sweep" for name, _, _ in launches}
+    L.vanse_destroy(h)
+    keep.clear()
+    assert len(kinds) == 1, kinds
+    return kinds.pop()
+
+on = dict(mask=1), dict(drag=1), dict(dynamic_phi=1)
+mask, drag, dyn = on
+for want, args, has in [
+    # two steps per launch: time of tiles over that of the sweep
+    ("sweep", (60, 123, 1919, "f64", "periodic", "wall"), drag),               # 1.24
+    ("sweep", (60, 500, 504, "f64", "periodic", "wall"), drag),                # 1.13
+    ("sweep", (60, 560, 552, "f64"), mask),                                    # 1.10
+    ("tiles", (60, 380, 390, "f64"), mask),                                    # 0.80
+    ("sweep", (60, 500, 499, "f64"), {}),                                      # 1.1
+    ("tiles", (60, 340, 340, "f64"), {}),                                      # 0.75
+    ("sweep", (60, 740, 740, "f32", "periodic", "periodic"), {}),              # 1.2
+    ("tiles", (60, 540, 540, "f32", "periodic", "wall"), {}),                  # 0.78
+    ("tiles", (60, 1003, 777, "f16s", "wall", "wall"), drag),                  # 0.72
+    ("sweep", (60, 1500, 1500, "f32", "wall", "wall"), drag),                  # 1.0
+    ("sweep", (60, 90, 3000, "f64"), dict(mask=1, dynamic_phi=1)),             # 1.24
+    # pairs
+    ("sweep", (60, 740, 743, "f32", "periodic", "periodic", 2), mask),         # 1.10
+    ("tiles", (60, 640, 640, "f32", "periodic", "periodic", 2), mask),         # 0.8
+    ("sweep", (2, 640, 640, "f64", "periodic", "periodic", 2, 2), dyn),        # 1.15
+    ("tiles", (2, 440, 440, "f64", "periodic", "periodic", 2, 2), dyn),        # 0.95
+    # one step
+    ("sweep", (1, 377, 377, "f16s"), {}),                                      # 1.19
+    ("tiles", (1, 377, 377, "f16s", "periodic", "wall"), {}),                  # 0.9
+    ("sweep", (1, 440, 440, "f64"), {}),                                       # 1.1
+    ("tiles", (1, 340, 340, "f64"), {}),                                       # 0.85
+    ("sweep", (1, 440, 440, "f64", "periodic", "periodic", 1, 1), dyn),        # 1.05
+    ("tiles", (1, 64, 64, "f64", "periodic", "periodic", 1, 1), dyn),          # 0.9
+]:
+    got = kernel(*args, **has)
+    assert got == want, (args, has, got)
+''')
