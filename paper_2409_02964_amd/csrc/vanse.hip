@@ -1663,18 +1663,25 @@ int batch_layout(vanse_lattice* const* lats, int n, int threads, int rows, int f
     // 13.6/5.2, 256 12.7/9.0, 700 20.7/19.5, 1500 53.3/50.8 (20 rows); 2048, where
     // one round takes 34 rows, 18 rows 107, 36 rows 111; two steps 150 21.0/8.0,
     // 256 21.1/10.2, 700 22.9/16.9 (12 rows).  FP32 alike; FP64 150 14.2/5.9, 700
-    // 43.2/40.2, two steps 29.7/11.2 and 35.5/30.9 (24 rows).
+    // 43.2/40.2, two steps 29.7/11.2 and 35.5/30.9 (24 rows).  With FP32 storage and
+    // 64 lanes, 8 rows that already make three fifths of a round stay: fewer would
+    // only fill it with rows that are swept twice (24.0 us against 24.6 with 6 rows,
+    // six lattices up to 700; medians over random batches 0.98 to 1.00).
     const int rounds = fuse == 2 ? 4 : 2;
     const long long slots = (long long)device_cus() * batch_per_cu(d0.precision, threads, fuse);
     r = (int)std::max<long long>((strip_rows + rounds * slots - 1) / (rounds * slots), fuse == 2 ? 32 : 8);
-    for (int q = fuse == 2 ? 4 : 1; q <= (fuse == 2 ? 31 : 24); ++q) {
+    auto tiles_of = [&](int q) {
       long long tiles = 0;
       for (int k = 0; k < n; ++k) {
         const vanse_desc& d = lats[k]->d;
         tiles += (long long)((d.nx + out_w - 1) / out_w) * ((d.ny + q - 1) / q);
       }
-      if (tiles <= slots) { r = q; break; }
-    }
+      return tiles;
+    };
+    const bool f32 = d0.precision == VANSE_F32 || d0.precision == VANSE_F32_SHIFTED;
+    const bool filled = fuse == 1 && threads == 64 && f32 && r == 8 && 5 * tiles_of(8) > 3 * slots && tiles_of(8) <= slots;
+    for (int q = fuse == 2 ? 4 : 1; !filled && q <= (fuse == 2 ? 31 : 24); ++q)
+      if (tiles_of(q) <= slots) { r = q; break; }
   }
   rows_out->assign(n, r);
   first_out->assign(n, 0);

@@ -113,3 +113,28 @@ for want, args, has in [
     got = kernel(*args, **has)
     assert got == want, (args, has, got)
 ''')
+
+
+def test_batches_that_eight_rows_nearly_fill_keep_them(tmp_path):
+    run(tmp_path, '''
+def rows(sides, precision, threads, spp=1):
+    h = [ready(lattice(s, s, precision), s, s) for s in sides]
+    a = (C.c_void_p * len(h))(*[x.value for x in h])
+    n, b, t, r = C.c_size_t(), C.c_void_p(), C.c_int(), C.c_int()
+    V.check(L.vanse_batch_workspace_bytes_ex(a, len(h), threads, 0, spp, C.byref(n)))
+    ws = (C.c_char * (n.value + 256))()
+    base = (C.addressof(ws) + 255) // 256 * 256
+    V.check(L.vanse_batch_create_ex(a, len(h), threads, 0, spp, C.c_void_p(base), n.value, C.byref(b)))
+    V.check(L.vanse_batch_tiles(b, C.byref(t), C.byref(r)))
+    L.vanse_batch_destroy(b)
+    for x in h:
+        L.vanse_destroy(x)
+    keep.clear()
+    return r.value
+
+six = [117, 233, 350, 467, 583, 700]
+assert rows(six, "f32", 64) == rows(six, "f32s", 64) == 8
+assert rows(six, "f16s", 64) == 6 and rows(six, "f32", 128) < 8 and rows(six, "f64", 64) == 11
+assert rows(six, "f32", 64, 2) == 12
+assert rows([100, 150], "f32", 64) == 1
+''')
