@@ -267,7 +267,7 @@ int vanse_observe(vanse_lattice *h, double *out, void *stream);
  * observables of vanse_observe, bitwise the same values, computed without
  * the lattice workspace's scratch -- the FP64 block partials and the
  * reduction records live in a static device array of the library (about
- * 5.3 MB, held by every device the library runs on until the process ends).
+ * 2.7 MB, held by every device the library runs on until the process ends).
  * Allocates nothing (the record comes through the library's page of pinned
  * host memory when another call has taken it, and is copied from the device
  * otherwise).  Limit: ceil(nx/256) * ny <= 131072 (for example

@@ -915,12 +915,16 @@ class HostRecord {
 
 }  // namespace
 
-// Scratch of vanse_observe_noalloc: the FP64 block partials of one read-out
-// (at most kScratchBlocks; read_shape gives about 2048), the chunk records of
-// the first reduction level and the final record.  Each device holds its own
-// copy for the life of the process; every call on a device overwrites it, so
-// calls that overlap on one device race.
-constexpr long long kScratchBlocks = 1LL << 17;
+// Scratch of vanse_observe_noalloc: the FP64 partials of one read-out (at most
+// kScratchBlocks), the chunk records of the first reduction level and the final
+// record.  Each device holds its own copy for the life of the process; every call on
+// a device overwrites it, so calls that overlap on one device race.
+// The call takes lattices of up to kObserveBlocks blocks of 256 columns of a row.
+// read_shape gives those at most 2048 records more than strips, and beyond 2048
+// strips one per strip: most for two rows, the fewest that a lattice has.
+constexpr long long kObserveBlocks = 1LL << 17;
+constexpr long long kScratchBlocks = (kObserveBlocks / 2 * 256 + READ_W - 1) / READ_W;
+static_assert(kScratchBlocks >= 2 * 2048, "lattices of up to 2048 strips");
 static __device__ __align__(256) double scratch[(kScratchBlocks + 1024 + 1) * NOBS];
 
 namespace {
@@ -1462,10 +1466,11 @@ int vanse_observe_noalloc(vanse_lattice* h, double* out, void* stream) {
   if (int rc = check_handle(h)) return rc;
   if (!out) return fail(VANSE_ERR_INVALID_ARG, "out is NULL");
   const long long nblk = (long long)((h->d.nx + 255) / 256) * h->d.ny;
-  if (nblk > kScratchBlocks)
+  const long long blocks = read_shape(h->d.nx, h->d.ny).blocks;
+  if (nblk > kObserveBlocks || blocks > kScratchBlocks)
     return fail(VANSE_ERR_INVALID_ARG,
-                "lattice too large for the static scratch: %lld read-out blocks of 256 columns > %lld",
-                nblk, kScratchBlocks);
+                "lattice too large for the static scratch: %lld blocks of 256 columns of a row > %lld",
+                nblk, kObserveBlocks);
   if (int rc = check_ready(h)) return rc;
   if (!h->state_set) return fail(VANSE_ERR_STATE, "populations not initialised");
   double* sp = nullptr;
@@ -1475,8 +1480,7 @@ int vanse_observe_noalloc(vanse_lattice* h, double* out, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (int rc = moments_into(h, nullptr, nullptr, nullptr, nullptr, part, st, false)) return rc;
   double rec[NOBS];
-  if (int rc = reduce_to_host(part, read_shape(h->d.nx, h->d.ny).blocks, mid, mid + 1024 * NOBS, false, rec, st))
-    return rc;
+  if (int rc = reduce_to_host(part, blocks, mid, mid + 1024 * NOBS, false, rec, st)) return rc;
   for (int q = 0; q < 4; ++q) out[q] = rec[q];
   if (out[3] > 0) return fail(VANSE_ERR_DIVERGED, "%.0f nodes hold non-finite values at t = %lld", out[3], (long long)h->t);
   return VANSE_OK;

@@ -20,6 +20,7 @@ static int call(const char *name) {
   return e;
 }
 
+size_t stub_var_bytes;  /* device variables */
 static struct { const void *key; const char *name; void *mem; } table[4096];
 static int entries;
 
@@ -38,6 +39,7 @@ void __hipRegisterVar(void **m, void *host, char *dev, const char *name, int ext
   table[entries].key = host;
   table[entries].name = name;
   table[entries++].mem = calloc(1, size);
+  stub_var_bytes += size;
 }
 
 static struct { dim3 g, b; size_t sh; void *st; } conf;

@@ -102,3 +102,21 @@ fail_call = lambda name, k: 0
 V.check(L.vanse_set_void_fraction(h, field(64 * 48), None))
 V.check(observe(h))
 ''')
+
+
+def test_the_static_scratch_holds_every_lattice_that_the_call_takes(tmp_path):
+    """The limit is 131072 blocks of 256 columns of a row; the records are one per
+    workgroup of the read-out, most of them on two rows."""
+    run(tmp_path, COMMON + '''
+size = C.c_size_t.in_dll(stub, "stub_var_bytes").value
+for nx, ny in ((65536 * 256, 2), (254 * 2049, 3), (254 * 1900, 9), (512, 4099), (2, 65535)):
+    h = ready(lattice(nx, ny, "f16s"), nx, ny)
+    V.check(L.vanse_observe_noalloc(h, out, None))
+    blocks = [b for name, b, _ in launches if "read_out" in name]
+    assert len(blocks) == 1 and (blocks[0] + 1025) * 40 <= size, (nx, ny, blocks, size)
+    L.vanse_destroy(h)
+    keep.clear()
+h = lattice(65536 * 256 + 1, 2, "f16s")
+assert L.vanse_observe_noalloc(h, out, None) == -1
+assert size < 3e6
+''')
