@@ -513,6 +513,22 @@ __device__ __forceinline__ void collide2_of(const Derivs2<T>& d, const RowState<
   o9[8] = bM + dXY;
 }
 
+// o - s d as it is stored, rounded once: the second step of a pair takes the
+// change of the rest state out of population 0.  In FP16 one instruction forms the
+// product, the difference and the conversion; it is named here because a product and
+// difference that are converted afterwards round twice, and which of the two the
+// compiler makes of an expression depends on the code around it.
+template <typename S, typename T>
+__device__ __forceinline__ S less_scaled(T o, T s, T d) {
+  if constexpr (sizeof(S) == 2) {
+    S r;
+    __asm__("v_fma_mixlo_f16 %0, -%1, %2, %3" : "=v"(r) : "v"(s), "v"(d), "v"(o));
+    return r;
+  } else {
+    return static_cast<S>(o - s * d);
+  }
+}
+
 // FEAT: the plain step plus any of FEAT_FORCE (a per-node force field added
 // to F^B), FEAT_DRAG (the linear drag, u solved in closed form as in the
 // single step), and FEAT_MASK (solid nodes; no walls in x) or FEAT_DYNPHI
@@ -1024,7 +1040,8 @@ __device__ inline void step2_tile(
         // a moving phi: the ring and shifted storage hold deviations from the
         // rest state of the void fraction the next pull runs at, whose rest_0
         // is rho0 d_t phi higher (times the storage scale for half 1's stores)
-        if (DYN && (half == 0 || SHIFT)) o9[0] -= ((SHIFT && half != 0) ? ph.scale : T(1)) * (rho0 * rC.dphi);
+        const T drest = DYN ? rho0 * rC.dphi : T(0);
+        if (DYN && half == 0) o9[0] -= drest;
 
         if (half == 0) {  // into the ring for the second step
           const int jo = jr(yo);
@@ -1036,8 +1053,9 @@ __device__ inline void step2_tile(
           }
           if (MASK) L.pop[pop_slot(PL_NB, jo)][t] = flags_as<T>((fl.hi >> 20) & 0x3FFu);
         } else if (SHIFT) {  // already scaled
+          bstore(DYN ? less_scaled<S>(o9[0], ph.scale, drest) : static_cast<S>(o9[0]), dstr, xcb, poff(0, yo));
 #pragma unroll
-          for (int i = 0; i < 9; ++i) bstore(static_cast<S>(o9[i]), dstr, xcb, poff(i, yo));
+          for (int i = 1; i < 9; ++i) bstore(static_cast<S>(o9[i]), dstr, xcb, poff(i, yo));
         } else {
           bstore(static_cast<S>(o9[0] + (phi * rho0 - ph.rest0_k)), dstr, xcb, poff(0, yo));
 #pragma unroll

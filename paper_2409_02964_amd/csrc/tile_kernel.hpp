@@ -272,9 +272,7 @@ vanse_tile_kernel(StepGeom g, StepPhys<T> ph, int walls, int steps) {
         const T drest = DYN ? ph.rho0 * r.dphi : T(0);
         if (DYN && !second) o9[0] -= drest;
         if (second && SHIFT) {  // already scaled
-          // (FP16: product, difference and conversion in one instruction that
-          // rounds once, as the sweep's code does)
-          out[0] = static_cast<S>(DYN ? o9[0] - ph.scale * drest : o9[0]);
+          out[0] = DYN ? less_scaled<S>(o9[0], ph.scale, drest) : static_cast<S>(o9[0]);
 #pragma unroll
           for (int i = 1; i < 9; ++i) out[i] = static_cast<S>(o9[i]);
         } else if (second) {
