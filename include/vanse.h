@@ -90,8 +90,9 @@ typedef struct {
 
 /* Bytes of device workspace the lattice described by *d needs (256-byte
  * aligned).  Layout: two population buffers, phi, optional phi(t+1),
- * solid-flag, force and drag planes, a velocity store and reduction
- * space.  VANSE_ERR_INVALID_ARG for a lattice whose population buffer (nine
+ * solid-flag, force and drag planes, a spare plane (a new void fraction,
+ * until it is checked), a velocity store and reduction space.
+ * VANSE_ERR_INVALID_ARG for a lattice whose population buffer (nine
  * planes of the storage type, rows padded to 64 nodes) would reach 4 GiB --
  * the step kernels address it with 32-bit offsets -- or with more than 65535
  * rows (set-up and read-out kernels put one row per grid row). */
@@ -262,8 +263,8 @@ int vanse_read_populations(vanse_lattice *h, double *f, void *stream);
  * VANSE_ERR_DIVERGED (after filling out) when out[3] > 0. */
 int vanse_observe(vanse_lattice *h, double *out, void *stream);
 
-/* For callers that cannot allocate device memory (code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the
+/* For callers that cannot allocate device memory (code between captured
+ * graphs, tight serving loops, harnesses that forbid hipMalloc): the
  * observables of vanse_observe, bitwise the same values, computed without
  * the lattice workspace's scratch -- the FP64 block partials and the
  * reduction records live in a static device array of the library (about
@@ -319,8 +320,9 @@ int vanse_get_tiling(const vanse_lattice *h, int *threads, int *rows,
  * small to fill the GPU then take up to two pairs per launch of a kernel of
  * their own, with bitwise the same results). */
 int vanse_set_steps_per_pass(vanse_lattice *h, int steps, int rows);
-/* Whether the two-step launch is in use (*active), and its rows per
- * workgroup and workgroups per launch. */
+/* Whether the two-step launch is in use (*active), and the two-step sweep's
+ * rows per workgroup and workgroups per launch, which it reports also where
+ * a small lattice takes the tile kernel instead (see vanse_get_tiling). */
 int vanse_get_fused_tiling(const vanse_lattice *h, int *active, int *rows,
                            int *workgroups);
 
@@ -356,7 +358,8 @@ typedef struct vanse_batch vanse_batch;
 
 /* Workspace bytes for a batch of n lattices with the given workgroup width
  * (64, 128 or 256) and rows per workgroup (0: one round of resident
- * workgroups over the batch if that takes at most 24 rows, else about two). */
+ * workgroups over the batch if that takes at most 24 rows, else about two;
+ * with FP32 storage and 64 lanes not fewer than 8 where 8 nearly make one). */
 int vanse_batch_workspace_bytes(vanse_lattice *const *lats, int n, int threads,
                                 int rows, size_t *bytes);
 int vanse_batch_create(vanse_lattice *const *lats, int n, int threads, int rows,

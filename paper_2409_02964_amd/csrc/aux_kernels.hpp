@@ -204,7 +204,7 @@ __device__ __forceinline__ unsigned slot_offset(const Geo& G, int x, int y, int 
 // solid nodes write the rest state into their own slots, which no pull reads.
 // Bound by HBM, the writes above all.  Forming a slot's value at the slot
 // (nine receivers' phi and divisions per node, directions looked up at run
-// time) took 349 us on 4096 x 4096 in FP32, this 210.
+// time) took 340 us on 4096 x 4096 in FP32, this 233.
 template <typename S, typename T, bool SHIFT>
 __global__ void fill_state(Geo G, S* __restrict__ buf, const T* __restrict__ phi, StepPhys<T> ph,
                            const double* __restrict__ fin, double rho_init, double ux0, double uy0,
@@ -315,10 +315,11 @@ struct ReadRow {
 // barriers ago), and the row below it is output; the next row's loads are in
 // flight meanwhile.  GEN: solid nodes, walls in x, moving walls or velocity
 // rows; the other lattices take loads without per-lane choices.
-// Measured, rho, u and p of the 4096 x 4096 FP32 channel: 279 us (4.3 TB/s of
-// the bytes above) against 2570 for two passes through a delta rho plane
+// Measured, a call that reads rho, u and p of the 4096 x 4096 FP32 channel: 283 us
+// (4.3 TB/s of the bytes above) against 2570 for two passes through a delta rho plane
 // whose loops over the directions were not unrolled (their populations lived
-// in scratch memory); 2048 x 2048 FP64: 115 against 1050 us.
+// in scratch memory), the observables alone 195 against 2500; 2048 x 2048 FP64 107
+// against 1013, and 109 against 984.
 template <typename S, typename T, bool SHIFT, bool GEN>
 __global__ void __launch_bounds__(256) read_out(
     Geo G, const S* __restrict__ buf, const T* __restrict__ phi, StepPhys<T> ph,

@@ -39,8 +39,8 @@
 
 namespace vanse_dev {
 
-// Tile sides in lanes.  In FP32 arithmetic (93-109 registers) 32 x 32 lanes,
-// the largest workgroup; in FP64 (156-168 registers) 32 x 24, the largest
+// Tile sides in lanes.  In FP32 arithmetic (93-116 registers) 32 x 32 lanes,
+// the largest workgroup; in FP64 (158-168 registers) 32 x 24, the largest
 // that three waves per SIMD and their 168 registers allow (32 x 32 spills 112
 // bytes a lane and takes 4.1 us a step on 64 x 64 nodes against 2.7).  Smaller
 // tiles recompute more: 32 x 16 lanes at two steps 3.6 us a step on 129 x 129
