@@ -493,40 +493,50 @@ long long tile_blocks(const vanse_lattice* h, int steps) {
 // Rounds of tiles (tiles per CU: one workgroup fills a CU's registers) up to which
 // a launch of the tile kernel is faster than the row sweep, by the sweep instance
 // that it replaces.  Tiles cost their number, about 6 us a round for two steps.  A
-// sweep costs the rows of its pipeline and those that it takes per workgroup, so
-// beyond one round the limit is a number of rounds and some more for every such
-// row.  The dearer the sweep's instance is, the higher: with solid nodes (whose flags
-// the tiles need too), for walls in x (which they need no flags for), and most of all
-// where the sweep carries a moving phi's planes that the tiles do without.  Walls in y
-// spare tiles the wrapped indices; FP64 tiles are smaller.  Measured: 64000 times of
-// both kernels on lattices of random sides, options and storages; the limits are
-// those that cost least, and 0.6% of the launches lose more than 4% to the sweep.
+// sweep costs the rows of its pipeline and those that it takes per workgroup, so the
+// limit is a number of rounds and some more for every such row (two steps per launch
+// up to one round always pay).  The dearer the sweep's instance is, the higher: with
+// solid nodes (whose flags the tiles need too), for walls in x (which they need no
+// flags for), and most of all where the sweep carries a moving phi's planes that the
+// tiles do without.  Walls in y spare tiles the wrapped indices; FP64 tiles are
+// smaller.  Measured: 64000 times of both kernels on lattices of random sides, options
+// and storages; the limits are those that cost least, and 0.7% of the launches lose
+// more than 4% to the sweep.
 // Tiles' time over the sweep's, medians up to one round, from there to the limit, and
 // from the limit to half as far again: two steps per launch, plain FP32 0.63 0.84
-// 1.15, FP64 0.64 0.75 1.09; solid nodes 0.53 0.76 1.05, 0.58 0.73 1.13; walls in x 0.51
-// 0.78 1.15, 0.53 0.75 1.11, with force field or drag 0.50 0.83 1.02, 0.50 0.78 1.05.
-// One step per launch, up to one round: plain FP32 periodic in y 1.02, with walls 0.86;
-// FP64 0.94, 0.83; solid nodes 0.80, 0.74; walls in x 0.76, 0.70.
+// 1.17, FP64 0.64 0.75 1.10; solid nodes 0.53 0.78 1.09, 0.58 0.74 1.15; walls in x 0.51
+// 0.78 1.16, 0.53 0.75 1.11, with force field or drag 0.50 0.85 1.03, 0.50 0.78 1.05.
+// One step per launch: plain FP32 up to one round, periodic in y 1.02, with walls 0.86,
+// FP64 0.94 and 0.83, beyond it 1.19, 1.02, 1.08 and 1.04; solid nodes with walls in y
+// 0.76 0.89 1.04, 0.71 0.90 1.05; walls in x 0.76 0.88 1.03, 0.70 0.86 1.01.
 struct TileLimit {
   double rounds, per_row;
 };
 struct TileRounds {
-  double one[2][2];     // one step per launch, [FP64][walls in y]
-  TileLimit two[2][2];  // two
+  TileLimit one[2][2], two[2][2];  // one or two steps per launch, [FP64][walls in y]
 };
 constexpr TileRounds kTileRounds[] = {
-    // plain, force field, drag
-    {{{0, 1}, {1, 1}}, {{{1.25, 0.75}, {2, 0.625}}, {{1.5, 0.25}, {1.75, 0.5}}}},
+    // plain, force field or drag
+    {{{{0, 0}, {1, 0}}, {{1, 0}, {0.75, 0.25}}},
+     {{{1.25, 0.75}, {1.5, 0.875}}, {{2, 0}, {1.75, 0.5}}}},
+    // force field and drag
+    {{{{0, 0}, {1, 0}}, {{1, 0}, {0.75, 0.25}}},
+     {{{1.25, 0.75}, {2, 0.625}}, {{0.5, 0.75}, {1.5, 0.625}}}},
     // moving phi (handed over or held)
-    {{{1, 1.75}, {1, 1.75}}, {{{1.75, 0.625}, {3.5, 0.25}}, {{1.5, 0.625}, {4, 0}}}},
+    {{{{1, 0}, {1.25, 0.25}}, {{1, 0}, {1.25, 0.25}}},
+     {{{1.75, 0.625}, {3.5, 0.25}}, {{1.5, 0.625}, {4, 0}}}},
     // solid nodes
-    {{{1, 2}, {1, 2}}, {{{1.75, 0.75}, {3, 0.5}}, {{1.25, 0.625}, {2, 0.5}}}},
+    {{{{1, 0}, {2, 0}}, {{1, 0}, {1.25, 0.25}}},
+     {{{1.75, 0.75}, {2, 1}}, {{1.5, 0.625}, {2, 0.5}}}},
     // walls in x
-    {{{1, 2.75}, {2, 3}}, {{{2, 1}, {3, 1}}, {{1.5, 0.875}, {3, 0.75}}}},
+    {{{{0.25, 0.75}, {1.25, 0.5}}, {{1.5, 0.25}, {2, 0.25}}},
+     {{{2.25, 1}, {3, 1}}, {{1.5, 0.875}, {3, 0.75}}}},
     // with a force field, drag or moving phi
-    {{{2.25, 6}, {3, 4}}, {{{2.5, 1.5}, {2.5, 1.5}}, {{2.25, 1}, {1.75, 1.125}}}},
+    {{{{2.25, 0}, {3, 0.5}}, {{1, 0.5}, {1.25, 0.5}}},
+     {{{2.5, 1.5}, {3, 1.5}}, {{2.25, 1}, {2, 1.125}}}},
     // solid nodes, where the sweep carries a moving phi's planes
-    {{{2, 6}, {2, 2.75}}, {{{2.25, 1.25}, {3.5, 1.25}}, {{2, 0.5}, {1.75, 0.75}}}},
+    {{{{2, 0}, {1.5, 0.75}}, {{2, 0}, {0.75, 0.5}}},
+     {{{2.25, 1.25}, {3.5, 1.25}}, {{2, 0.5}, {1.75, 0.75}}}},
 };
 // The same for a pair of steps against the two-step sweep (whose pipeline is longer
 // and whose rows cost less): rounds alone.  Medians, FP32 and FP64: 0.44 0.79 1.10,
@@ -543,7 +553,9 @@ constexpr double kTilePairRounds[][2][2] = {
 const TileRounds& tile_rounds_of(const vanse_lattice* h) {
   const int f = feat_of(h);
   const bool planes = f == (FEAT_MASK | FEAT_MOVING);
-  return kTileRounds[h->d.has_mask ? (planes ? 5 : 2) : planes ? 4 : (f & FEAT_MASK) ? 3 : f == FEAT_MOVING ? 1 : 0];
+  if (h->d.has_mask) return kTileRounds[planes ? 6 : 3];
+  if (f & FEAT_MASK) return kTileRounds[planes ? 5 : 4];
+  return kTileRounds[f == FEAT_MOVING ? 2 : f == (FEAT_FORCE | FEAT_DRAG) ? 1 : 0];
 }
 
 // Steps per launch of the tile kernel for n single steps, or 0 for the row
@@ -556,13 +568,14 @@ int tile_steps(const vanse_lattice* h, int64_t n) {
   const long long cus = device_cus();
   const int f64 = h->d.precision == VANSE_F64, wy = h->d.bc_y == VANSE_WALL;
   const TileRounds& most = tile_rounds_of(h);
-  const int single = tile_blocks(h, 1) <= most.one[f64][wy] * cus ? 1 : 0;
+  auto pay = [&](int steps, const TileLimit& l) {
+    return tile_blocks(h, steps) <= (l.rounds + l.per_row * h->rows) * cus;
+  };
+  const int single = pay(1, most.one[f64][wy]) ? 1 : 0;
   if (n == 1 || h->phin_set) return single;
   for (int k = 4; k >= 3; --k)
     if (tile_blocks(h, k) <= cus) return n == 2 ? single : k;
-  if (n < 4) return single;
-  const TileLimit two = most.two[f64][wy];
-  return tile_blocks(h, 2) <= std::max(two.rounds + two.per_row * h->rows, 1.0) * cus ? 2 : 0;
+  return n < 4 ? single : tile_blocks(h, 2) <= cus || pay(2, most.two[f64][wy]) ? 2 : 0;
 }
 
 // Of n single steps at k per launch, those to hand to run_tiles at once: with two

@@ -66,6 +66,8 @@ def kernel(n, nx, ny, precision, bc_x="periodic", bc_y="periodic", spp=1, hand=0
         V.check(L.vanse_set_mask(h, field(nx * ny), None))
     if "drag" in has:
         V.check(L.vanse_set_drag(h, field(nx * ny), 0.0, 0.0, None))
+    if "force_field" in has:
+        V.check(L.vanse_set_force_field(h, field(nx * ny), field(nx * ny), None))
     ready(h, nx, ny)
     V.check(L.vanse_set_steps_per_pass(h, spp, 0))
     if hand:
@@ -97,6 +99,8 @@ for want, args, has in [
     ("tiles", (60, 1003, 777, "f16s", "wall", "wall"), drag),                  # 0.72
     ("sweep", (60, 1500, 1500, "f32", "wall", "wall"), drag),                  # 1.0
     ("sweep", (60, 90, 3000, "f64"), dict(mask=1, dynamic_phi=1)),             # 1.24
+    ("tiles", (60, 520, 350, "f64"), dict(force_field=1, drag=1)),             # 0.85
+    ("sweep", (60, 520, 350, "f64"), drag),                                    # 1.0
     # pairs
     ("sweep", (60, 740, 743, "f32", "periodic", "periodic", 2), mask),         # 1.10
     ("tiles", (60, 640, 640, "f32", "periodic", "periodic", 2), mask),         # 0.8
@@ -109,6 +113,7 @@ for want, args, has in [
     ("tiles", (1, 340, 340, "f64"), {}),                                       # 0.85
     ("sweep", (1, 440, 440, "f64", "periodic", "periodic", 1, 1), dyn),        # 1.05
     ("tiles", (1, 64, 64, "f64", "periodic", "periodic", 1, 1), dyn),          # 0.9
+    ("tiles", (1, 287, 934, "f32", "wall", "periodic"), {}),                   # 0.83
 ]:
     got = kernel(*args, **has)
     assert got == want, (args, has, got)
